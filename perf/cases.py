@@ -97,7 +97,13 @@ def draw(rng):
         group = rng.choice([g for g in (32, 64, 128) if all(w % g == 0 for w in widths)])
     pos = int(math.exp(rng.uniform(0.0, math.log(8193)))) - 1
     steps = 1 if rng.random() < 0.7 else rng.randint(2, 6)
-    return dict(base, fmt=fmt, group=group, pos=pos, steps=steps, read_token=steps == 1 and rng.random() < 0.5)
+    c = dict(base, fmt=fmt, group=group, pos=pos, steps=steps, read_token=steps == 1 and rng.random() < 0.5)
+    while work(c)["bytes"] > 16e9:  # no more than the largest listed case
+        if c["steps"] > 1:
+            c["steps"] -= 1
+        else:
+            c["layers"] = max(1, c["layers"] * 2 // 3)
+    return c
 
 
 # ------------------------------------------------------------------ inputs
