@@ -17,6 +17,7 @@
 
 using amk::DevLayer;
 using amk::DevModel;
+using amk::OpGeom;
 using amk::Schedule;
 using amk::Shape;
 using amk::amk_internal_attn_scratch;
@@ -24,6 +25,7 @@ using amk::amk_internal_launch;
 using amk::amk_internal_occupancy;
 using amk::amk_internal_prepare;
 using amk::amk_internal_read_probe;
+using amk::amk_internal_static_lds;
 using amk::amk_internal_static_scratch;
 using amk::amk_internal_threads;
 
@@ -333,18 +335,40 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     // 32 consecutive activations
     const int nsw = amk_internal_threads() / 64 - 1;
     const size_t act = round_up((size_t)std::max({s.H, s.nq * s.hd, s.I}), s.fmt == AMK_WEIGHTS_W4A16 ? 2048 : 1024);
-    const size_t act_lds = act + act / 16;  // one float4 of padding per 64 floats (staggered LDS banks)
+    // one float4 of padding per 64 floats (staggered LDS banks); at least the
+    // three bf16 parts of a group's queries (attention)
+    const size_t qrows = round_up((size_t)s.group * s.hd * 3 / 2, 4);
+    const size_t act_lds = std::max(act + act / 16, qrows);
     const size_t xsum = s.fmt == AMK_WEIGHTS_W4A16 ? act / 32 : 0;
-    // per-wave partial stride in whole float4s keeps every region 16-byte aligned
-    const size_t pstride = round_up((size_t)s.max_jobs, 4);
-    const size_t scr = std::max<size_t>((size_t)nsw * pstride, (size_t)amk_internal_attn_scratch(s.group, s.hd));
-    const size_t lds_bytes = (act_lds + 3 * pstride + scr + xsum) * 4;
+    // the rows its schedules' tasks have; every region a whole number of float4s
+    size_t max_rows = 4, stat = 0, res = 4;
+    for (int v = 0; v < kVariants; ++v)
+      for (const amk_task_t& t : h->sch[v].tasks) {
+        const size_t rows = (size_t)amk::task_jobs(s, t), items = (size_t)(t.end - t.begin);
+        max_rows = std::max(max_rows, rows);
+        if (t.op == AMK_OP_O || t.op == AMK_OP_DOWN) res = std::max(res, rows);
+        if (rows && (items > 64 || t.op == AMK_OP_LMHEAD)) stat = std::max(stat, items * (t.op == AMK_OP_QKV ? 4 : t.op == AMK_OP_LMHEAD ? 1 : 2));
+      }
+    const size_t pstride = round_up(max_rows, 4);
+    stat = round_up(stat, 4);
+    res = round_up(res, 4);
+    // the attention scratch goes behind the queries in the activation region
+    // if there is no room for it beside it
+    const size_t attn = (size_t)amk_internal_attn_scratch(s.group, s.hd);
+    size_t scr = std::max<size_t>((size_t)nsw * pstride, attn), scr_at = 0;
+    const size_t fixed = (act_lds + stat + res + xsum) * 4;
+    size_t lds_bytes = fixed + scr * 4;
     int max_lds = 0;
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
       free_handle(h);
       return AMK_ERR_DEVICE;
     }
-    if ((long)lds_bytes + 256 > (long)max_lds) {
+    if ((long)lds_bytes + amk_internal_static_lds() > (long)max_lds && qrows + attn <= act_lds) {
+      scr_at = qrows;
+      scr = (size_t)nsw * pstride;
+      lds_bytes = fixed + scr * 4;
+    }
+    if ((long)lds_bytes + amk_internal_static_lds() > (long)max_lds) {
       std::fprintf(stderr, "amk: needs %zu B of LDS per workgroup, device allows %d\n", lds_bytes, max_lds);
       free_handle(h);
       return AMK_ERR_UNSUPPORTED;
@@ -367,6 +391,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     size_t top = 0;
     auto take = [&](size_t bytes) { Region r{top, bytes}; top = round_up(top + bytes, 256); return r; };
     const Region r_layers = take(sizeof(DevLayer) * L);
+    const Region r_geom = take(sizeof(OpGeom) * amk::kOps);
     const Region r_rope = take(sizeof(float) * 2 * (size_t)s.max_seq * s.half);
     // vectors of the residual stream and per-layer activations on separate
     // 256-byte boundaries (64 floats)
@@ -467,7 +492,22 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
         rope[2 * ((size_t)p * s.half + i) + 1] = (float)std::sin(a);
       }
     }
-    bool ok = hipMemcpy(base + r_layers.off, layers.data(), r_layers.bytes, hipMemcpyHostToDevice) == hipSuccess &&
+    // row geometry per GEMV op; a tied LM head is the bf16 embedding
+    const int lm_fmt = s.tied ? AMK_WEIGHTS_BF16 : s.fmt;
+    std::vector<OpGeom> geom(amk::kOps);
+    for (int op : {(int)AMK_OP_QKV, (int)AMK_OP_O, (int)AMK_OP_GATEUP, (int)AMK_OP_DOWN, (int)AMK_OP_LMHEAD}) {
+      const int K = op == AMK_OP_O ? s.nq * s.hd : op == AMK_OP_DOWN ? s.I : s.H;
+      const int f = op == AMK_OP_LMHEAD ? lm_fmt : s.fmt;
+      OpGeom& g = geom[op];
+      g.row_bytes = f == AMK_WEIGHTS_W4A16 ? K / 2 : f == AMK_WEIGHTS_W8A16 ? K : 2 * K;
+      g.gpr = (g.row_bytes + 1023) / 1024;
+      g.magic = g.gpr > 1 ? (uint32_t)(((1ull << 32) + g.gpr - 1) / g.gpr) : 0;
+      g.lastb = g.row_bytes - (g.gpr - 1) * 1024;
+      g.srow = f == AMK_WEIGHTS_W4A16 ? K / s.qgroup * 2 : 0;
+      g.quant = f != AMK_WEIGHTS_BF16;
+    }
+    bool ok = hipMemcpy(base + r_geom.off, geom.data(), r_geom.bytes, hipMemcpyHostToDevice) == hipSuccess &&
+              hipMemcpy(base + r_layers.off, layers.data(), r_layers.bytes, hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(base + r_rope.off, rope.data(), r_rope.bytes, hipMemcpyHostToDevice) == hipSuccess;
     for (int v = 0; v < kVariants && ok; ++v)
       ok = hipMemcpy(base + r_tasks[v].off, h->sch[v].tasks.data(), r_tasks[v].bytes, hipMemcpyHostToDevice) ==
@@ -483,7 +523,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     std::memset(&m, 0, sizeof(m));
     m.H = s.H; m.L = L; m.nq = s.nq; m.nkv = s.nkv; m.hd = s.hd; m.I = s.I; m.V = s.V; m.max_seq = s.max_seq;
     m.fmt = s.fmt;
-    m.lm_fmt = s.tied ? AMK_WEIGHTS_BF16 : s.fmt;
+    m.lm_fmt = lm_fmt;
     m.qglog2 = 0;
     while (s.qgroup && (1 << m.qglog2) < s.qgroup) ++m.qglog2;
     m.group = s.group; m.half = s.half;
@@ -491,6 +531,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     while ((1 << m.half_log2) < s.half) ++m.half_log2;
     m.units = s.units; m.q_units = s.q_units; m.nsplit = s.nsplit; m.n_lm = n_lm;
     m.gq2 = s.group + 2;
+    m.gq2_magic = (uint32_t)(((1ull << 32) + m.gq2 - 1) / m.gq2);
     m.npg = s.npg;
     m.n_cu = n_cu;
     m.eps = s.eps;
@@ -500,6 +541,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     m.lm_w = s.tied ? w->embed : w->lm_head.w;
     m.lm_s = m.lm_fmt != AMK_WEIGHTS_BF16 ? w->lm_head.scale : nullptr;
     m.layers = (const DevLayer*)(base + r_layers.off);
+    m.geom = (const OpGeom*)(base + r_geom.off);
     m.rope = (const float2*)(base + r_rope.off);
     m.x = (float*)(base + r_x.off);
     m.q = (float*)(base + r_q.off);
@@ -522,7 +564,10 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     }
     m.lds_act = (int32_t)act_lds;
     m.part_stride = (int32_t)pstride;
+    m.lds_stat = (int32_t)stat;
+    m.lds_res = (int32_t)res;
     m.lds_scr = (int32_t)scr;
+    m.scr_at = (int32_t)scr_at;
     m.lds_bytes = (int32_t)lds_bytes;
 
     const int timeout_us = tuning && tuning->timeout_us > 0 ? tuning->timeout_us : 2000000;

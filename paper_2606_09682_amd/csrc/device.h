@@ -19,6 +19,17 @@ struct DevLayer {
   const uint16_t* mlp_norm;    // bf16 [H]
 };
 
+// Weight-row geometry of a GEMV op (indexed by AMK_OP_*).
+struct OpGeom {
+  int32_t row_bytes;
+  int32_t gpr;        // 1 KiB granules per row, the last one possibly short
+  uint32_t magic;     // ceil(2^32 / gpr), 0 for gpr = 1: n / gpr = mulhi(n, magic) below 2^20
+  int32_t lastb;      // bytes of a row's last granule
+  int32_t srow;       // W4A16: bytes of a row's scales
+  int32_t quant;      // rows in the handle's quantised format
+};
+constexpr int kOps = AMK_OP_ARGMAX + 1;
+
 // Counters live on separate 128-byte lines, each in kCounterReplicas copies
 // (counter c, copy r at element (c * kCounterReplicas + r) * kCounterStride):
 // a producer increments every copy, and workgroup b polls copy b % 16, so a
@@ -40,6 +51,7 @@ struct DevModel {
   int32_t qglog2;     // W4A16: log2 of the input columns per scale
   int32_t group, half, half_log2, units, q_units, nsplit, n_lm;
   int32_t gq2;        // group + 2: head slots of one KV group in QKV unit order
+  uint32_t gq2_magic; // ceil(2^32 / gq2): n / gq2 = mulhi(n, magic) for head slots
   int32_t npg;        // QKV tasks per KV group (producers of a group's QKV counter)
   int32_t n_cu;
   float eps;
@@ -50,6 +62,7 @@ struct DevModel {
   const void* lm_w;
   const void* lm_s;
   const DevLayer* layers;    // device array [L]
+  const OpGeom* geom;        // device array [kOps]
   // handle-owned tables and scratch
   const float2* rope;        // [max_seq][half] (cos, sin), computed in fp64 on the host
   // Every vector below is written at most once per launch and read only after
@@ -72,12 +85,15 @@ struct DevModel {
   uint64_t* trace;           // [n_tasks][AMK_TRACE_FIELDS] timestamps, or null
   const amk_task_t* tasks;   // sorted by (cu, seq)
   const int32_t* queue_start;// [n_cu + 1]
-  // LDS layout (floats): act[lds_act] stat[2 * part_stride]
-  // res[part_stride] part[lds_scr] xsum[lds_act / 32 under W4A16]
+  // LDS layout (floats): act[lds_act] stat[lds_stat] res[lds_res]
+  // part[lds_scr] xsum[lds_act / 32 under W4A16]
   int32_t lds_act;           // activation vector region in floats: a whole number of granules'
                              // elements plus one float4 of padding per 64 floats
-  int32_t part_stride;       // rows of one GEMV task at most (partials per streaming wave)
+  int32_t part_stride;       // most rows of one GEMV task (partials per streaming wave)
+  int32_t lds_stat;          // four floats per item of the largest task of more than 64 items
+  int32_t lds_res;           // most rows of one O / down task
   int32_t lds_scr;           // GEMV partials of all streaming waves, or attention scratch
+  int32_t scr_at;            // offset of the attention scratch inside act, 0: it lies in part
   int32_t lds_bytes;         // dynamic LDS bytes of one workgroup
 };
 
@@ -87,6 +103,7 @@ extern "C" int amk_internal_launch(const DevModel* m, int32_t tiny, int32_t toke
                                    uint16_t* kv, float* logits, uint64_t timeout_ticks, void* stream);
 // Threads per workgroup and LDS the kernel needs beyond the model-dependent regions.
 extern "C" int amk_internal_threads(void);
+extern "C" int amk_internal_static_lds(void);  // bytes of LDS the kernel declares itself
 extern "C" int amk_internal_attn_scratch(int group, int head_dim);
 extern "C" int amk_internal_prepare(int head_dim, int group, int fmt, int lds_bytes);
 extern "C" int amk_internal_occupancy(int head_dim, int group, int fmt, int lds_bytes, int* blocks_per_cu);

@@ -17,26 +17,26 @@
 //   all waves   load the task's input activation into LDS after the wait (one
 //               round trip), run attention, and run inline continuations.
 //
-// Per task the workgroup passes four barriers:
+// Per task the workgroup passes three barriers:
 //   B1a  the sync wave's counter wait is satisfied (or the launch aborts)
 //   B1b  the input activation is in LDS (GEMV tasks)
 //   B2   the task's compute is done (partials in LDS / attention stored)
-//   B3   the sync wave has stored, released and signalled the task's results
-// A task with a chain counter whose signal completed its counter (it is the
-// last producer of this launch) then runs that counter's inline task with
-// every wave: a KV group's whole attention after its QKV tasks, or the merge
-// of a KV group's attention splits.  Each wave drains its own stores, the
-// workgroup meets at B4, the sync wave releases and signals the chain
-// counter, and B5 keeps the next task's weight loads behind that signal.
-// The streaming waves issue the weight loads of their NEXT task right after
-// B3 (int4 weights in the tiny-context kernel: right after B2).  Memory
-// requests of one CU are served roughly in order, so loads issued before the
-// result stores, the release or the counter increment would delay every
-// consumer on other CUs; issued after them, the loads stream while the
-// counters propagate and the next input is fetched.  The pipeline is kept
-// shallow (two halves of Pipe<FMT>::N granules per wave): measured on the
-// Llama-3-8B shape, deeper pipelines both delay the sync wave's polls and
-// input loads and stream no faster.
+// after which the sync wave stores, releases and signals the task's results
+// while the other waves go on to the next task.  A task with a chain counter
+// passes B3 after its signal: if that signal completed its counter (it is the
+// last producer of this launch) every wave then runs that counter's inline
+// task: a KV group's whole attention after its QKV tasks, or the merge of a KV
+// group's attention splits.  Each wave drains its own stores, the workgroup
+// meets at B4 and the sync wave releases and signals the chain counter.
+//
+// The weight stream does not stop at a task's end: while a streaming wave
+// consumes the last granules of one task it already issues the first ones of
+// the next GEMV task of its queue (weights depend on nothing), so they travel
+// while the epilogue, the signal, the wait and the input load go on.  For that
+// the sync wave keeps the next tasks' records and layer pointers in LDS
+// (struct Slot), loaded two and three tasks ahead: read when needed, each was
+// a chain of two cold scalar loads between a task's end and its successor's
+// first weight load.
 //
 // Every result another workgroup reads is stored coherent at agent scope
 // (write-through past the XCD's L2), so releasing it takes only a drain of
@@ -62,26 +62,30 @@ constexpr int NT = 512;       // threads per workgroup
 constexpr int NW = NT / 64;   // waves
 constexpr int NSW = NW - 1;   // streaming waves
 constexpr int GRAN = 1024;    // bytes per wave-wide 16-B-per-lane load
-// Granules per pipeline half, per wave: 4 for bf16 weights, 2 for int8 and
-// int4 (their granules hold two and four times the multiply-adds).  Measured
-// on the Llama-3-8B shape, deeper pipelines at a task switch delay the sync
-// wave's polls and input loads and stream no faster.  EXTRA blocks of N
-// granules more are issued once the task's input is in LDS, deepening only
-// the steady state: int8 weights stream faster with two (four blocks in
-// flight); bf16 and int4 weights, bound by VGPRs and by VALU issue, slower.
-template <int FMT> struct Pipe {
-  static constexpr int N = FMT == AMK_WEIGHTS_BF16 ? 4 : 2;
-  static constexpr int EXTRA = FMT == AMK_WEIGHTS_W8A16 ? 2 : 0;
+// Granules each streaming wave keeps in flight (registers): R slots, each
+// refilled as soon as it is consumed.
+template <int FMT> struct Ring {
+  static constexpr int R = 4;
 };
 // int4 columns per granule, and per lane (one 16-byte load of 32 nibbles)
 constexpr int GRAN4 = 2 * GRAN;
 constexpr int LANE4 = 32;
 
+// A task record and its layer's pointers, staged in LDS ahead of their task.
+struct Slot {
+  amk_task_t t;
+  DevLayer ly;
+};
+constexpr int NSLOT = 4;  // tasks idx .. idx + 3
+static_assert(sizeof(amk_task_t) == 64 && sizeof(DevLayer) == 128, "one dword per lane: 16 lanes a record, 32 a layer");
+
 struct Ctl {
+  Slot slot[NSLOT];
+  OpGeom geom[kOps];            // per op, from the handle's table
+  float4 prep[2][64];           // the prepared epilogue of the task to come (struct Fast), a lane per item
+  float ssq[NSW];               // per-wave sum of squares of the task input
   int abort;
   int cont;                     // this task runs its chain counter's inline task
-  int res_buf, res_lo, res_hi;  // residual rows cached in LDS: x buffer index and row range
-  float ssq[NW];                // per-wave sum of squares of the task input
 };
 
 // ---------------------------------------------------------------- memory helpers
@@ -144,6 +148,12 @@ __device__ __forceinline__ uint16_t f2bf(float f) {  // round to nearest even
 }
 __device__ __forceinline__ float i8f(uint32_t w, int k) { return (float)(int8_t)(w >> (8 * k)); }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ const T* unip(const T* p) {
+  const uint64_t u = (uint64_t)p;
+  const uint32_t lo = (uint32_t)uni((int)(uint32_t)u), hi = (uint32_t)uni((int)(uint32_t)(u >> 32));
+  return (const T*)((uint64_t)hi << 32 | lo);
+}
 // Wait until every global load and store this wave issued has completed
 // (s_waitcnt vmcnt(0)).  A barrier does not wait for them, so waves that
 // store results another CU reads drain before the barrier that precedes the
@@ -234,6 +244,18 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// The model record is read where it lies, in the kernel-argument segment
+// (uniform scalar loads through the constant cache), through a pointer that
+// reopen() makes anew for the compiler at every task: held by value, its
+// fields were all loaded at the kernel's start and some 260 of them lived in
+// spill lanes.
+typedef const AMK_CONST DevModel& ModelRef;
+__device__ __forceinline__ const AMK_CONST DevModel* reopen(const AMK_CONST DevModel* p) {
+  uint64_t u = (uint64_t)p;
+  asm volatile("" : "+s"(u));
+  return (const AMK_CONST DevModel*)u;
+}
+
 __device__ __forceinline__ bool is_gemv(int op) {
   return op == AMK_OP_QKV || op == AMK_OP_O || op == AMK_OP_GATEUP || op == AMK_OP_DOWN ||
          op == AMK_OP_LMHEAD;
@@ -253,10 +275,9 @@ __device__ __forceinline__ bool is_normed(int op) {
 // 64-float block, so its loads keep immediate offsets, and a granule's start
 // c * E (E a multiple of 64) moves to c * E * 17 / 16.
 // After act[]:
-//   stat[2 * max_rows]      int8 row scales (rows [0, nj)), then for QKV the
-//                           RoPE (cos, sin) of unit u at [nj + 2u, nj + 2u + 1]
-//   res[max_rows]           residual rows of the last O / down task (or the
-//                           layer-0 embedding rows)
+//   stat[...]               static epilogue data of a task of more than 64 items
+//                           (epi_stat gives the layout)
+//   res[...]                residual rows of the last O / down task
 //   part[...]               per-streaming-wave row partials / attention scratch
 //   xsum[...]               W4A16: xsum[i] = sum of act[32 i .. 32 i + 31]
 __device__ __forceinline__ int act_at(int i) { return i + ((i >> 6) << 2); }
@@ -275,151 +296,189 @@ struct Lds {
 // ---------------------------------------------------------------- GEMV task geometry
 struct Gemv {
   int nj = 0;          // rows (jobs)
-  int row_bytes = 0;
   int gpr = 1;         // granules per row
-  int int8 = 0;        // int8 weights, fp32 row scales applied in the epilogue
-  int q4 = 0;          // int4 weights, fp16 group scales applied per granule
-  int tail = 0;        // row_bytes not a multiple of GRAN
+  int quant = 0;       // rows in the handle's quantised format (a tied LM head is bf16)
   int G = 0;           // total granules = nj * gpr
-  int srow = 0;        // int4: scale bytes per row
 };
 
 // QKV unit u: head slot u / (d/2) counts KV group by KV group, each group
 // holding its query heads, then its K head, then its V head.
-__device__ __forceinline__ void unit_head(const DevModel& m, int u, int* mat, int* head) {
+__device__ __forceinline__ void unit_head(ModelRef m, int u, int* mat, int* head) {
   const int slot = u >> m.half_log2;
-  const int g = slot / m.gq2;
+  const int g = (int)__umulhi((uint32_t)slot, m.gq2_magic);  // slot / gq2
   const int r = slot - g * m.gq2;
   if (r < m.group) { *mat = W_Q; *head = g * m.group + r; }
   else { *mat = r == m.group ? W_K : W_V; *head = g; }
 }
 
-// Which matrix and row job j of task t reads.  mat < 0 means the LM head.
-__device__ __forceinline__ void job_row(const DevModel& m, const amk_task_t& t, int j, int* mat, int* row) {
-  switch (t.op) {
-    case AMK_OP_QKV: {
-      const int u = t.begin + (j >> 1);
-      int head;
-      unit_head(m, u, mat, &head);
-      *row = head * m.hd + (u & (m.half - 1)) + (j & 1) * m.half;
-      break;
-    }
-    case AMK_OP_GATEUP: *mat = (j & 1) ? W_U : W_G; *row = t.begin + (j >> 1); break;
-    case AMK_OP_O: *mat = W_O; *row = t.begin + j; break;
-    case AMK_OP_DOWN: *mat = W_D; *row = t.begin + j; break;
-    default: *mat = -1; *row = t.begin + j; break;
-  }
+__device__ __forceinline__ int task_jobs_dev(int op, int n) {
+  return (op == AMK_OP_QKV || op == AMK_OP_GATEUP) ? 2 * n : n;
 }
 
-__device__ __forceinline__ const uint8_t* mat_base(const DevModel& m, const amk_task_t& t, int mat) {
-  if (mat < 0) return (const uint8_t*)m.lm_w;
-  return (const uint8_t*)ldc<const void*>(&m.layers[t.layer].w[mat]);
-}
-__device__ __forceinline__ const uint8_t* mat_scale(const DevModel& m, const amk_task_t& t, int mat) {
-  if (mat < 0) return (const uint8_t*)m.lm_s;
-  return (const uint8_t*)ldc<const void*>(&m.layers[t.layer].s[mat]);
-}
-
-__device__ __forceinline__ int task_jobs_dev(const amk_task_t& t) {
-  const int n = t.end - t.begin;
-  return (t.op == AMK_OP_QKV || t.op == AMK_OP_GATEUP) ? 2 * n : n;
-}
-
-__device__ __forceinline__ int task_k(const DevModel& m, const amk_task_t& t) {
-  switch (t.op) {
-    case AMK_OP_O: return m.nq * m.hd;
-    case AMK_OP_DOWN: return m.I;
-    default: return m.H;
-  }
-}
-
-__device__ __forceinline__ Gemv gemv_geom(const DevModel& m, const amk_task_t& t) {
+__device__ __forceinline__ Gemv gemv_geom(const Ctl& ctl, int op, int n) {
   Gemv g;
-  const int K = task_k(m, t);
-  const int wf = (t.op == AMK_OP_LMHEAD) ? m.lm_fmt : m.fmt;
-  g.int8 = wf == AMK_WEIGHTS_W8A16;
-  g.q4 = wf == AMK_WEIGHTS_W4A16;
-  g.row_bytes = g.q4 ? K / 2 : g.int8 ? K : 2 * K;
-  g.srow = g.q4 ? (K >> m.qglog2) * 2 : 0;
-  g.gpr = (g.row_bytes + GRAN - 1) / GRAN;
-  g.tail = (g.row_bytes % GRAN) != 0;
-  g.nj = task_jobs_dev(t);
+  g.gpr = uni(ctl.geom[op].gpr);
+  g.quant = uni(ctl.geom[op].quant);
+  g.nj = task_jobs_dev(op, n);
   g.G = g.nj * g.gpr;
   return g;
 }
 
 // Granule range of streaming wave sw: [sw*G/NSW, (sw+1)*G/NSW).  G * NSW
 // stays far below 2^31 (rows per task <= 1024, granules per row <= 64).
-__device__ __forceinline__ int wave_gbegin(int G, int sw) { return (G * sw) / NSW; }
+__device__ __forceinline__ int wave_gbegin(int G, int sw) { return (int)((uint32_t)(G * sw) / NSW); }
 
-struct Cursor {
-  int j, c;
-  const uint8_t* p;
-  const uint8_t* ps;  // W4A16: the row's fp16 group scales (int4 rows), else p
+// The issue side of a wave's weight stream: the next granule to load, walking
+// the rows of one task.  Rows are visited in job order: single-matrix tasks
+// step one row at a time; gate / up and QKV tasks alternate between two rows
+// (gate and up; the RoPE pair i, i + d/2), so the row after next is always the
+// current one plus `step`.  A QKV stream that reaches the end of a head looks
+// up the next one.
+struct Stream {
+  const uint8_t *cur = nullptr, *nxt = nullptr;    // the current row and the one after it
+  const uint8_t *scur = nullptr, *snxt = nullptr;  // W4A16: their group scales
+  uint32_t step = 0, sstep = 0;
+  int c = 0;        // granule of the current row
+  int gpr = 1;
+  int lastb = 0;    // bytes of a row's last granule
+  int quant = 0;
+  int left = 0;     // granules of this wave's range not issued yet
+  int hleft = 0;    // jobs left in the QKV head, the current one included
+  int unit = 0;     // QKV: first unit of the next head
+  int slot = 0;     // the task's LDS slot
 };
 
 template <int FMT>
-__device__ __forceinline__ void row_ptr(Cursor& cu, const DevModel& m, const amk_task_t& t, const Gemv& g, int j) {
-  int mat, row;
-  job_row(m, t, j, &mat, &row);
-  cu.p = mat_base(m, t, mat) + (size_t)row * g.row_bytes;
-  if constexpr (FMT == AMK_WEIGHTS_W4A16) cu.ps = g.q4 ? mat_scale(m, t, mat) + (size_t)row * g.srow : cu.p;
+__device__ __forceinline__ void stream_head(Stream& s, ModelRef m, const Ctl& ctl, int u, int odd) {
+  int mat, head;
+  unit_head(m, u, &mat, &head);
+  const int i = u & (m.half - 1);
+  const OpGeom& og = ctl.geom[AMK_OP_QKV];
+  const uint32_t rb = (uint32_t)uni(og.row_bytes);
+  const uint8_t* base = unip((const uint8_t*)ctl.slot[s.slot].ly.w[mat]);
+  const uint8_t* lo = base + (size_t)(head * m.hd + i) * rb;
+  const uint8_t* hi = lo + (size_t)m.half * rb;
+  s.cur = odd ? hi : lo;
+  s.nxt = odd ? lo + rb : hi;
+  if constexpr (FMT == AMK_WEIGHTS_W4A16) {
+    const uint32_t srow = (uint32_t)uni(og.srow);
+    const uint8_t* sb = unip((const uint8_t*)ctl.slot[s.slot].ly.s[mat]);
+    const uint8_t* slo = sb + (size_t)(head * m.hd + i) * srow;
+    const uint8_t* shi = slo + (size_t)m.half * srow;
+    s.scur = odd ? shi : slo;
+    s.snxt = odd ? slo + srow : shi;
+  }
+  s.unit = u - i + m.half;
+  s.hleft = 2 * (m.half - i) - odd;
 }
 
+// Start of streaming wave sw's range in the task at LDS slot k; returns its
+// first job and granule, and the number of granules in s.left.
 template <int FMT>
-__device__ __forceinline__ void cursor_init(Cursor& cu, const DevModel& m, const amk_task_t& t, const Gemv& g,
-                                            int gidx) {
-  cu.j = gidx / g.gpr;
-  cu.c = gidx - cu.j * g.gpr;
-  row_ptr<FMT>(cu, m, t, g, cu.j < g.nj ? cu.j : g.nj - 1);
-}
-
-template <int FMT>
-__device__ __forceinline__ void cursor_next(Cursor& cu, const DevModel& m, const amk_task_t& t, const Gemv& g) {
-  if (++cu.c == g.gpr) {
-    cu.c = 0;
-    ++cu.j;
-    if (cu.j < g.nj) row_ptr<FMT>(cu, m, t, g, cu.j);
+__device__ __forceinline__ void stream_begin(Stream& s, ModelRef m, const Ctl& ctl, int k, int sw, int* j0,
+                                             int* c0) {
+  const Slot& sl = ctl.slot[k];
+  const int op = uni(sl.t.op), begin = uni(sl.t.begin), n = uni(sl.t.end) - begin;
+  const OpGeom& og = ctl.geom[op];
+  const uint32_t rb = (uint32_t)uni(og.row_bytes), magic = (uint32_t)uni(og.magic);
+  s.slot = k;
+  s.gpr = uni(og.gpr);
+  s.lastb = uni(og.lastb);
+  s.quant = uni(og.quant);
+  const int G = task_jobs_dev(op, n) * s.gpr;
+  const int g0 = wave_gbegin(G, sw);
+  s.left = wave_gbegin(G, sw + 1) - g0;
+  // g0 / gpr with magic = ceil(2^32 / gpr) (0 for gpr = 1)
+  int j = magic ? (int)__umulhi((uint32_t)g0, magic) : g0;
+  s.c = g0 - j * s.gpr;
+  *j0 = j;
+  *c0 = s.c;
+  s.hleft = 0x7fffffff;
+  if (op == AMK_OP_QKV) {
+    s.step = rb;
+    if constexpr (FMT == AMK_WEIGHTS_W4A16) s.sstep = (uint32_t)uni(og.srow);
+    stream_head<FMT>(s, m, ctl, begin + (j >> 1), j & 1);
+    return;
+  }
+  const bool pair = op == AMK_OP_GATEUP;
+  const int mat = op == AMK_OP_O ? W_O : op == AMK_OP_DOWN ? W_D : W_G;
+  const uint8_t* a = op == AMK_OP_LMHEAD ? (const uint8_t*)m.lm_w : unip((const uint8_t*)sl.ly.w[mat]);
+  if (pair) {
+    const uint8_t* b = unip((const uint8_t*)sl.ly.w[W_U]);
+    const size_t off = (size_t)(begin + (j >> 1)) * rb;
+    s.step = rb;
+    s.cur = (j & 1) ? b + off : a + off;
+    s.nxt = (j & 1) ? a + off + rb : b + off;
+  } else {
+    s.step = 2 * rb;
+    s.cur = a + (size_t)(begin + j) * rb;
+    s.nxt = s.cur + rb;
+  }
+  if constexpr (FMT == AMK_WEIGHTS_W4A16) {
+    // rows of another format load a valid address instead of scales
+    const uint32_t srow = (uint32_t)uni(og.srow);
+    const uint8_t* sa = !s.quant ? s.cur : op == AMK_OP_LMHEAD ? (const uint8_t*)m.lm_s : unip((const uint8_t*)sl.ly.s[mat]);
+    if (!s.quant) {
+      s.scur = s.snxt = sa;
+      s.sstep = 0;
+    } else if (pair) {
+      const uint8_t* sb = unip((const uint8_t*)sl.ly.s[W_U]);
+      const size_t off = (size_t)(begin + (j >> 1)) * srow;
+      s.sstep = srow;
+      s.scur = (j & 1) ? sb + off : sa + off;
+      s.snxt = (j & 1) ? sa + off + srow : sb + off;
+    } else {
+      s.sstep = 2 * srow;
+      s.scur = sa + (size_t)(begin + j) * srow;
+      s.snxt = s.scur + srow;
+    }
   }
 }
 
-// The weight pipeline issues every load unconditionally, so the compiler can
-// count outstanding loads exactly and wait for just the oldest one (a load
-// under a branch forces it to drain the whole pipeline).  Lanes past the end
-// of a short row, and granules past the end of the wave's range, re-read a
-// valid address of the current row; consume_block() never uses them (rows)
-// or zeroes them (tail lanes).
-__device__ __forceinline__ uint4 load_gran(const Cursor& cu, const Gemv& g, int lane) {
-  int off = cu.c * GRAN + lane * 16;
-  if (g.tail && off >= g.row_bytes) off = 0;
-  return ldg<uint4>(cu.p + off);
-}
-
-// The fp16 scale of the lane's 32 int4 columns (one group holds whole
-// lanes); tail lanes and rows of other formats re-read a valid address.
-__device__ __forceinline__ uint32_t load_scale4(const Cursor& cu, const DevModel& m, const Gemv& g, int lane) {
-  int idx = (cu.c * GRAN4 + lane * LANE4) >> m.qglog2;
-  if (!g.q4 || (g.tail && cu.c * GRAN + lane * 16 >= g.row_bytes)) idx = 0;
-  return ldg<uint16_t>(cu.ps + 2 * idx);
-}
-
-// Issue N granules starting at global granule index gi (clipped to g1); under
-// W4A16 also each granule's per-lane group scale.
-template <int FMT, int N>
-__device__ __forceinline__ void issue_block(uint4 (&buf)[N], uint32_t (&sc)[N], Cursor& cu, int& gi, int g1,
-                                            const DevModel& m, const amk_task_t& t, const Gemv& g, int lane) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    buf[i] = load_gran(cu, g, lane);
-    if constexpr (FMT == AMK_WEIGHTS_W4A16) sc[i] = load_scale4(cu, m, g, lane);
-    if (gi < g1) cursor_next<FMT>(cu, m, t, g);
-    ++gi;
+// Load the stream's next granule (under W4A16 with the fp16 scale of each
+// lane's 32 columns; one group holds whole lanes) and step on.  The load is
+// unconditional, so in the steady loop the compiler counts outstanding loads
+// exactly and waits for just the oldest one (a load under a branch makes it
+// drain the whole ring): past the end of the range one 16-byte vector of the
+// last granule is read again and never used, and lanes past the end of a short
+// row re-read the granule's start, which consume() drops.
+template <int FMT>
+__device__ __forceinline__ void stream_issue(Stream& s, uint4& buf, uint32_t& sc, ModelRef m, const Ctl& ctl,
+                                             int lane) {
+  uint32_t o = (uint32_t)lane * 16;
+  const uint32_t lim = s.left <= 0 ? 16u : s.c == s.gpr - 1 ? (uint32_t)s.lastb : (uint32_t)GRAN;
+  o = o < lim ? o : 0;
+  buf = ldg<uint4>(s.cur + (size_t)(uint32_t)(s.c * GRAN) + o);
+  if constexpr (FMT == AMK_WEIGHTS_W4A16) sc = ldg<uint16_t>(s.scur + 2 * ((uint32_t)(s.c * GRAN4 + 2 * o) >> m.qglog2));
+  if (--s.left > 0 && ++s.c == s.gpr) {
+    s.c = 0;
+    if (--s.hleft == 0) {
+      stream_head<FMT>(s, m, ctl, s.unit, 0);
+    } else {
+      const uint8_t* t = s.cur + s.step;
+      s.cur = s.nxt;
+      s.nxt = t;
+      if constexpr (FMT == AMK_WEIGHTS_W4A16) {
+        const uint8_t* u = s.scur + s.sstep;
+        s.scur = s.snxt;
+        s.snxt = u;
+      }
+    }
   }
 }
 
-__device__ __forceinline__ float dot_gran(const uint4 v, const float* __restrict__ act, int c, int lane, int int8,
+// The consume side: the next granule of the wave's range to reduce.
+struct Work {
+  int j = 0, c = 0;     // job and granule
+  int left = 0;         // granules not consumed yet
+  int gpr = 1, lastb = 0, quant = 0;
+  float acc = 0.f;
+};
+
+template <int FMT>
+__device__ __forceinline__ float dot_gran(const uint4 v, const float* __restrict__ act, int c, int lane, int quant,
                                           float acc) {
-  if (!int8) {
+  if (FMT != AMK_WEIGHTS_W8A16 || !quant) {
     const float* x = act + act_gran<GRAN / 2>(c, lane * 8);
     const float4 a = *reinterpret_cast<const float4*>(x);
     const float4 b = *reinterpret_cast<const float4*>(x + 4);
@@ -485,31 +544,27 @@ __device__ __forceinline__ float dot_gran4(const uint4 v, uint32_t sbits, const 
   return valid ? fmaf(s, p, acc) : acc;
 }
 
-// Consume N granules; a finished row's wave-reduced partial goes to part[j].
-template <int FMT, int N>
-__device__ __forceinline__ void consume_block(const uint4 (&buf)[N], const uint32_t (&sc)[N], int& j, int& c, int& gi,
-                                              int g1, float& acc, const Lds& L, float* __restrict__ part,
-                                              const Gemv& g, int lane) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if (gi < g1) {
-      if (FMT == AMK_WEIGHTS_W4A16 && g.q4) {
-        const bool valid = !g.tail || c * GRAN + lane * 16 < g.row_bytes;
-        acc = dot_gran4(buf[i], sc[i], L.act, L.xsum, c, lane, valid, acc);
-      } else {
-        uint4 v = buf[i];
-        if (g.tail && c * GRAN + lane * 16 >= g.row_bytes) v = make_uint4(0, 0, 0, 0);
-        acc = dot_gran(v, L.act, c, lane, g.int8, acc);
-      }
-      if (++c == g.gpr) {
-        const float s = wave_sum(acc);
-        if (lane == 0) part[j] = s;
-        acc = 0.f;
-        c = 0;
-        ++j;
-      }
-    }
-    ++gi;
+// Reduce one granule; a finished row's wave-reduced partial goes to part[j].
+template <int FMT>
+__device__ __forceinline__ void consume(Work& w, const uint4& buf, uint32_t sc, const Lds& L, float* __restrict__ part,
+                                        int lane) {
+  if (w.left <= 0) return;
+  --w.left;
+  const bool last = w.c == w.gpr - 1;
+  const bool valid = !last || lane * 16 < w.lastb;
+  if (FMT == AMK_WEIGHTS_W4A16 && w.quant) {
+    w.acc = dot_gran4(buf, sc, L.act, L.xsum, w.c, lane, valid, w.acc);
+  } else {
+    const float r = dot_gran<FMT>(buf, L.act, w.c, lane, w.quant, w.acc);
+    w.acc = valid ? r : w.acc;
+  }
+  ++w.c;
+  if (last) {
+    const float r = wave_sum(w.acc);
+    if (lane == 0) part[w.j] = r;
+    w.acc = 0.f;
+    w.c = 0;
+    ++w.j;
   }
 }
 
@@ -544,17 +599,30 @@ __device__ __forceinline__ void acquire_after_poll() { __atomic_signal_fence(__A
 // latency-bound streaming phases suffer from the extra poll traffic).
 template <int FMT> struct Polls { static constexpr bool TWO = FMT == AMK_WEIGHTS_BF16; };
 
+// What a wait needs, prepared one task ahead: lanes past n_wait poll the first
+// counter too and never block, so the loads are unconditional and the compiler
+// counts them exactly.
+struct Poll {
+  const uint32_t* p = nullptr;
+  uint32_t target = 0;
+  int nw = 0;
+};
+__device__ __forceinline__ Poll poll_for(ModelRef m, const amk_task_t& t, uint32_t epoch, int lane) {
+  Poll w;
+  w.nw = uni(t.n_wait);
+  const int wl = lane < w.nw ? lane : 0;
+  const int c = w.nw ? t.wait_counter[wl] : 0;
+  w.p = m.counters + ((size_t)c * kCounterReplicas + blockIdx.x % kCounterReplicas) * kCounterStride;
+  w.target = epoch * (uint32_t)t.wait_count[wl];
+  return w;
+}
+
 template <int FMT>
-__device__ __forceinline__ bool wait_deps(const DevModel& m, const amk_task_t& t, const amk_task_t* tp, uint32_t epoch,
-                                          uint64_t deadline, int lane, uint64_t* tr) {
-  const int nw = t.n_wait;
-  if (nw == 0) return __hip_atomic_load(m.dev_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-  // lanes past n_wait poll the first counter too and never block: the loads
-  // are unconditional, so the compiler counts them exactly
-  const int wl = lane < nw ? lane : 0;
-  const uint32_t* p = m.counters + ((size_t)ldg<int32_t>(&tp->wait_counter[wl]) * kCounterReplicas +
-                                    blockIdx.x % kCounterReplicas) * kCounterStride;
-  const uint32_t target = epoch * (uint32_t)ldg<int32_t>(&tp->wait_count[wl]);
+__device__ __forceinline__ bool wait_deps(ModelRef m, const Poll& w, uint64_t deadline, int lane, uint64_t* tr) {
+  const int nw = w.nw;
+  if (nw == 0) return uni(__hip_atomic_load(m.dev_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0;
+  const uint32_t* p = w.p;
+  const uint32_t target = w.target;
   uint32_t spins = 0;
   uint32_t v_old = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (;;) {
@@ -568,10 +636,10 @@ __device__ __forceinline__ bool wait_deps(const DevModel& m, const amk_task_t& t
     ++spins;
     int code = 0;
     if (Polls<FMT>::TWO ? (spins & 7u) == 0 : true) {
-      if (__hip_atomic_load(m.dev_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
+      if (uni(__hip_atomic_load(m.dev_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return false;
     }
     // host-mapped flag: read over the bus, so only every 64 spins
-    if ((spins & 63u) == 0 && __hip_atomic_load(m.host_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM))
+    if ((spins & 63u) == 0 && uni(__hip_atomic_load(m.host_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)))
       code = AMK_ERR_ABORTED;
     else if (now > deadline)
       code = AMK_ERR_TIMEOUT;
@@ -596,150 +664,171 @@ __device__ __forceinline__ bool wait_deps(const DevModel& m, const amk_task_t& t
   return true;
 }
 
-__device__ __forceinline__ void release_signal(const DevModel& m, int counter, int lane) {
-  drain_vmem();  // every published store of this wave is coherent at agent scope
-  if (lane < kCounterReplicas && counter >= 0)
-    __hip_atomic_fetch_add(m.counters + ((size_t)counter * kCounterReplicas + lane) * kCounterStride, 1u,
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// This lane's copy of a counter (lanes past the copies: none).
+__device__ __forceinline__ uint32_t* counter_copy(ModelRef m, int counter, int lane) {
+  if (counter < 0 || lane >= kCounterReplicas) return nullptr;
+  return m.counters + ((size_t)counter * kCounterReplicas + lane) * kCounterStride;
 }
 
-// Release, increment `counter`, and report whether this increment brought it
+__device__ __forceinline__ void release_signal(uint32_t* copy) {
+  drain_vmem();  // every published store of this wave is coherent at agent scope
+  if (copy) __hip_atomic_fetch_add(copy, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Release, increment a counter, and report whether this increment brought it
 // to `target` (the last producer of this launch).  The caller that gets true
 // acquires before reading what the other producers released.
-__device__ __forceinline__ bool release_signal_last(const DevModel& m, int counter, uint32_t target, int lane) {
+__device__ __forceinline__ bool release_signal_last(uint32_t* copy, uint32_t target) {
   drain_vmem();
   uint32_t old = 0;
   // copy 0's return value orders the producers
-  if (lane < kCounterReplicas)
-    old = __hip_atomic_fetch_add(m.counters + ((size_t)counter * kCounterReplicas + lane) * kCounterStride, 1u,
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (copy) old = __hip_atomic_fetch_add(copy, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   old = (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
   return (int32_t)(old + 1u - target) == 0;
 }
 
 // ---------------------------------------------------------------- per-row static data
 // Data of a GEMV task that does not depend on this launch's results and is
-// needed only in its epilogue (int8 row scales, RoPE factors, the layer-0
-// embedding rows of the residual) is fetched by the sync wave while the
-// streaming waves compute.
+// needed only in its epilogue: int8 row scales, RoPE factors, the layer-0
+// embedding rows of the residual.  For a task of at most 64 items (rows, or
+// row pairs) the last streaming wave loads it two tasks ahead, so nobody waits
+// for these cold loads; for larger tasks (LM head) the sync wave loads it in
+// the task itself, while the others compute.
+struct RowStat {
+  float a = 0.f, b = 0.f;  // int8 scales of the item's row(s)
+  float c = 0.f, s = 0.f;  // QKV: RoPE factors;  layer-0 O: c = the embedding value
+};
 
-__device__ __forceinline__ void load_rowdata(const DevModel& m, const amk_task_t& t, int token, int pos,
-                                             const Lds& L, Ctl& ctl, int lane) {
-  const int op = t.op;
-  const Gemv g = gemv_geom(m, t);
-  if (g.int8) {
-    for (int j = lane; j < g.nj; j += 64) {
-      int mat, row;
-      job_row(m, t, j, &mat, &row);
-      L.stat[j] = ldg<float>(mat_scale(m, t, mat) + 4 * (size_t)row);
-    }
-  }
+// Item i of a task: its (first) row's matrix and row, and the second row's.
+__device__ __forceinline__ RowStat row_stat(ModelRef m, const Slot& sl, int op, int quant, int i, int token,
+                                            int pos) {
+  RowStat r;
   if (op == AMK_OP_QKV) {
-    const int nu = t.end - t.begin;
-    for (int u = lane; u < nu; u += 64) {
-      const int i = (t.begin + u) & (m.half - 1);
-      const float2 cs = ldg<float2>(m.rope + (size_t)pos * m.half + i);
-      L.stat[g.nj + 2 * u] = cs.x;
-      L.stat[g.nj + 2 * u + 1] = cs.y;
+    const int u = i, k = u & (m.half - 1);
+    if (quant) {
+      int mat, head;
+      unit_head(m, u, &mat, &head);
+      const float* s = (const float*)sl.ly.s[mat] + head * m.hd + k;
+      r.a = ldg<float>(s);
+      r.b = ldg<float>(s + m.half);
     }
-  }
-  if (op == AMK_OP_O && t.layer == 0) {
-    const uint16_t* e = m.embed + (size_t)token * m.H;
-    for (int r = t.begin + lane; r < t.end; r += 64) L.res[r - t.begin] = bf16f(ldg<uint16_t>(e + r));
-    if (lane == 0) {
-      ctl.res_buf = 0;
-      ctl.res_lo = t.begin;
-      ctl.res_hi = t.end;
+    const float2 cs = ldg<float2>(m.rope + (size_t)pos * m.half + k);
+    r.c = cs.x;
+    r.s = cs.y;
+  } else if (op == AMK_OP_GATEUP) {
+    if (quant) {
+      r.a = ldg<float>((const float*)sl.ly.s[W_G] + i);
+      r.b = ldg<float>((const float*)sl.ly.s[W_U] + i);
     }
+  } else {
+    if (quant) {
+      const void* s = op == AMK_OP_LMHEAD ? m.lm_s : sl.ly.s[op == AMK_OP_O ? W_O : W_D];
+      r.a = ldg<float>((const float*)s + i);
+    }
+    if (op == AMK_OP_O && sl.t.layer == 0) r.c = bf16f(ldg<uint16_t>(m.embed + (size_t)token * m.H + i));
   }
+  return r;
 }
 
-// ---------------------------------------------------------------- input activation (all waves)
-// The task input moves into LDS in one round trip: wave w copies a 1/8 slice.
-// Normed inputs load the RMSNorm gain in the same round trip, store x * gain
-// and leave each wave's sum of x^2 in ctl.ssq; the GEMV result is scaled by
-// 1/sqrt(mean(x^2) + eps) in the epilogue (RMSNorm folded into the consumer).
-// Under W4A16 the slices are whole 32-column blocks and each block's sum of
-// the stored values goes to xsum (8 lanes hold one block).
+// ---------------------------------------------------------------- input activation (streaming waves)
+// The task input moves into LDS in one round trip: chunk q of 64 float4s goes
+// through streaming wave q mod 7 (the sync wave meanwhile prepares the
+// epilogue).  Normed inputs are stored as x * gain, with each wave's sum of
+// x^2 in ctl.ssq; the GEMV result is scaled by 1/sqrt(mean(x^2) + eps) in the
+// epilogue (RMSNorm folded into the consumer).  The gains depend on nothing,
+// so they are loaded before the wait (load_gain).  Under W4A16 each 32-column
+// block's sum of the stored values goes to xsum (8 lanes hold one block).
+constexpr int NGAIN = 4;  // chunks a wave preloads the gains of
+
+__device__ __forceinline__ void load_gain(const uint16_t* gain, int n4, int sw, int lane, uint2 (&gv)[NGAIN]) {
+#pragma unroll
+  for (int i = 0; i < NGAIN; ++i)
+    if ((sw + NSW * i) * 64 < n4) gv[i] = ldg<uint2>(gain + 4 * (size_t)min((sw + NSW * i) * 64 + lane, n4 - 1));
+}
+
+template <int FMT, int NB, bool NORM>
+__device__ __forceinline__ float input_batch(const float* src, const uint2* gv, int q0, int n4, const Lds& L, int lane) {
+  float4 xv[NB];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) xv[i] = ldg<float4>(src + 4 * (size_t)min((q0 + NSW * i) * 64 + lane, n4 - 1));
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    const int v = (q0 + NSW * i) * 64 + lane;
+    float4 x = xv[i];
+    if constexpr (NORM) {
+      if (v < n4) {
+        ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
+      }
+      x = make_float4(x.x * bf_lo(gv[i].x), x.y * bf_hi(gv[i].x), x.z * bf_lo(gv[i].y), x.w * bf_hi(gv[i].y));
+    }
+    if (v < n4) *reinterpret_cast<float4*>(L.act + act_at(v * 4)) = x;
+    if constexpr (FMT == AMK_WEIGHTS_W4A16) {
+      // lanes 8k .. 8k + 7 hold one block, all in range or all out
+      const float blk = group_sum<8>((x.x + x.y) + (x.z + x.w));
+      if (v < n4 && (lane & 7) == 0) L.xsum[v >> 3] = blk;
+    }
+  }
+  return ss;
+}
+
 template <int FMT>
-__device__ __forceinline__ void load_input(const DevModel& m, const amk_task_t& t, int token, const Lds& L, Ctl& ctl,
-                                           int wave, int lane) {
-  const int op = t.op;
-  const float* src = nullptr;
-  const uint16_t* src_bf = nullptr;
-  const uint16_t* gain = nullptr;
-  switch (op) {
-    case AMK_OP_QKV:
-      if (t.layer == 0) src_bf = m.embed + (size_t)token * m.H;
-      else src = m.x + (size_t)(2 * t.layer) * m.xs;
-      gain = ldc<const uint16_t*>(&m.layers[t.layer].attn_norm);
-      break;
-    case AMK_OP_GATEUP:
-      src = m.x + (size_t)(2 * t.layer + 1) * m.xs;
-      gain = ldc<const uint16_t*>(&m.layers[t.layer].mlp_norm);
-      break;
-    case AMK_OP_LMHEAD: src = m.x + (size_t)(2 * m.L) * m.xs; gain = m.final_norm; break;
-    case AMK_OP_O: src = m.o + (size_t)t.layer * m.qs; break;
-    case AMK_OP_DOWN: src = m.a + (size_t)t.layer * m.as; break;
-    default: return;
-  }
-  const int K = task_k(m, t);
-  const int n4 = K >> 2;  // float4 vectors (K is a multiple of 16; of 32 under W4A16)
-  constexpr int AL = FMT == AMK_WEIGHTS_W4A16 ? 8 : 1;
-  const int v0 = (n4 / AL * wave) / NW * AL, v1 = (n4 / AL * (wave + 1)) / NW * AL;
-  float ss = 0.f;
-  constexpr int NB = 8;
-  for (int b = v0; b < v1; b += NB * 64) {
-    float4 xv[NB];
-    uint2 gv[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int v = b + i * 64 + lane;
-      if (v < v1) {
-        if (src_bf) {
-          const uint2 r = ldg<uint2>(src_bf + (size_t)v * 4);
-          xv[i] = make_float4(bf_lo(r.x), bf_hi(r.x), bf_lo(r.y), bf_hi(r.y));
-        } else {
-          xv[i] = ldg<float4>(src + (size_t)v * 4);
-        }
-        if (gain) gv[i] = ldg<uint2>(gain + (size_t)v * 4);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int v = b + i * 64 + lane;
-      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < v1) {
-        x = xv[i];
-        if (gain) {
-          ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
-          x = make_float4(x.x * bf_lo(gv[i].x), x.y * bf_hi(gv[i].x), x.z * bf_lo(gv[i].y), x.w * bf_hi(gv[i].y));
-        }
-        *reinterpret_cast<float4*>(L.act + act_at(v * 4)) = x;
-      }
-      if constexpr (FMT == AMK_WEIGHTS_W4A16) {
-        // v0 and b are multiples of 8: lanes 8k .. 8k + 7 hold one block,
-        // all in range or all out
-        const float blk = group_sum<8>((x.x + x.y) + (x.z + x.w));
-        if (v < v1 && (lane & 7) == 0) L.xsum[v >> 3] = blk;
-      }
-    }
-  }
-  if (gain) {
-    ss = wave_sum(ss);
-    if (lane == 0) ctl.ssq[wave] = ss;
-  }
+__device__ __forceinline__ void load_input(const float* src, int n4, const Lds& L, int sw, int lane) {
+  const int nc = (n4 + 63) / 64;
+  const int n = (nc - sw + NSW - 1) / NSW;  // chunks of this wave
+  if (n <= 0) return;
+  if (n == 1) input_batch<FMT, 1, false>(src, nullptr, sw, n4, L, lane);
+  else if (n == 2) input_batch<FMT, 2, false>(src, nullptr, sw, n4, L, lane);
+  else if (n <= 4) input_batch<FMT, 4, false>(src, nullptr, sw, n4, L, lane);
+  else
+    for (int q = sw; q < nc; q += 8 * NSW) input_batch<FMT, 8, false>(src, nullptr, q, n4, L, lane);
 }
 
-__device__ __forceinline__ float input_rs(const DevModel& m, const Ctl& ctl) {
+template <int FMT>
+__device__ __forceinline__ void load_input_normed(const float* src, const uint16_t* src_bf, const uint16_t* gain, int n4,
+                                                  uint2 (&gv)[NGAIN], const Lds& L, Ctl& ctl, int sw, int lane) {
+  const int nc = (n4 + 63) / 64;
+  const int n = (nc - sw + NSW - 1) / NSW;
+  float ss = 0.f;
+  if (src_bf) {  // layer 0: the embedding row
+    for (int q = sw; q < nc; q += NSW) {
+      const int v = q * 64 + lane, vc = min(v, n4 - 1);
+      const uint2 r = ldg<uint2>(src_bf + (size_t)vc * 4), g = ldg<uint2>(gain + (size_t)vc * 4);
+      float4 x = make_float4(bf_lo(r.x), bf_hi(r.x), bf_lo(r.y), bf_hi(r.y));
+      if (v < n4) {
+        ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
+      }
+      x = make_float4(x.x * bf_lo(g.x), x.y * bf_hi(g.x), x.z * bf_lo(g.y), x.w * bf_hi(g.y));
+      if (v < n4) *reinterpret_cast<float4*>(L.act + act_at(v * 4)) = x;
+      if constexpr (FMT == AMK_WEIGHTS_W4A16) {
+        const float blk = group_sum<8>((x.x + x.y) + (x.z + x.w));
+        if (v < n4 && (lane & 7) == 0) L.xsum[v >> 3] = blk;
+      }
+    }
+  } else if (n == 1) {
+    ss = input_batch<FMT, 1, true>(src, gv, sw, n4, L, lane);
+  } else if (n == 2) {
+    ss = input_batch<FMT, 2, true>(src, gv, sw, n4, L, lane);
+  } else if (n > 2) {
+    ss = input_batch<FMT, NGAIN, true>(src, gv, sw, n4, L, lane);
+    for (int q = sw + NSW * NGAIN; q < nc; q += NSW) {  // hidden sizes past 7168
+      const uint2 g1[1] = {ldg<uint2>(gain + 4 * (size_t)min(q * 64 + lane, n4 - 1))};
+      ss += input_batch<FMT, 1, true>(src, g1, q, n4, L, lane);
+    }
+  }
+  ss = wave_sum(ss);
+  if (lane == 0) ctl.ssq[sw] = ss;
+}
+
+__device__ __forceinline__ float input_rs(ModelRef m, const Ctl& ctl) {
   float ss = 0.f;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) ss += ctl.ssq[w];
+  for (int w = 0; w < NSW; ++w) ss += ctl.ssq[w];
   return 1.0f / sqrtf(ss / (float)m.H + m.eps);
 }
 
 // ---------------------------------------------------------------- row sums of a GEMV task
-// Granule boundaries of the streaming waves, computed once per epilogue.
+// Granule boundaries of the streaming waves, computed while they compute.
 struct Ranges {
   int b[NSW + 1];
 };
@@ -760,33 +849,70 @@ __device__ __forceinline__ float row_sum(const float* part, int stride, const Ge
   for (int sw = 0; sw < NSW; ++sw) v[sw] = part[sw * stride + j];
   float s = 0.f;
 #pragma unroll
-  for (int sw = 0; sw < NSW; ++sw) {
-    const int gb = wr.b[sw], ge = wr.b[sw + 1];
-    s += (gb < ge && gb < hi && ge > lo) ? v[sw] : 0.f;
-  }
+  for (int sw = 0; sw < NSW; ++sw) s += max(wr.b[sw], lo) < min(wr.b[sw + 1], hi) ? v[sw] : 0.f;
   return s;
 }
 
 // ---------------------------------------------------------------- sync wave: epilogues
-__device__ __forceinline__ void epi_qkv(const DevModel& m, const amk_task_t& t, const Gemv& g, const Lds& L, int pos,
-                                        uint16_t* kv, float rs, int lane) {
-  const int l = t.layer;
-  const Ranges wr = wave_ranges(g);
-  for (int u = t.begin + lane; u < t.end; u += 64) {
-    const int j0 = 2 * (u - t.begin);
-    float y0 = row_sum(L.part, m.part_stride, g, wr, j0) * rs;
-    float y1 = row_sum(L.part, m.part_stride, g, wr, j0 + 1) * rs;
-    if (g.int8) {
-      y0 *= L.stat[j0];
-      y1 *= L.stat[j0 + 1];
+// What the sync wave holds for the epilogue of a task of more than 64 items.
+struct Epi {
+  Gemv g;
+  Ranges wr;
+  float rs;         // RMSNorm factor of normed inputs
+  int layer, begin, end, aux;
+};
+// Residual rows cached in LDS: x buffer index and row range.
+struct Res {
+  int buf = -1, lo = 0, hi = 0;
+};
+
+// Static data of item i in LDS: per item four floats for QKV, two for gate / up (a, b) and for the residual
+// ops (a, c), one for the LM head (a).
+template <int OP>
+__device__ __forceinline__ RowStat epi_stat(const Epi& e, const Lds& L, int i) {
+  RowStat r;
+  const int k = i - e.begin;
+  if constexpr (OP == AMK_OP_QKV) {
+    const float4 v = *reinterpret_cast<const float4*>(L.stat + 4 * k);
+    r.a = v.x; r.b = v.y; r.c = v.z; r.s = v.w;
+  } else if constexpr (OP == AMK_OP_GATEUP) {
+    r.a = L.stat[2 * k]; r.b = L.stat[2 * k + 1];
+  } else if constexpr (OP == AMK_OP_O) {
+    r.a = L.stat[2 * k]; r.c = L.stat[2 * k + 1];
+  } else {
+    r.a = L.stat[k];
+  }
+  return r;
+}
+__device__ __forceinline__ void put_stat(const Lds& L, int op, int k, const RowStat& r) {
+  if (op == AMK_OP_QKV) {
+    *reinterpret_cast<float4*>(L.stat + 4 * k) = make_float4(r.a, r.b, r.c, r.s);
+  } else if (op == AMK_OP_LMHEAD) {
+    L.stat[k] = r.a;
+  } else {
+    L.stat[2 * k] = r.a;
+    L.stat[2 * k + 1] = op == AMK_OP_GATEUP ? r.b : r.c;
+  }
+}
+
+__device__ __forceinline__ void epi_qkv(ModelRef m, const Epi& e, const Lds& L, int pos, uint16_t* kv,
+                                        int lane) {
+  const int l = e.layer;
+  for (int u = e.begin + lane; u < e.end; u += 64) {
+    const int j0 = 2 * (u - e.begin);
+    float y0 = row_sum(L.part, m.part_stride, e.g, e.wr, j0) * e.rs;
+    float y1 = row_sum(L.part, m.part_stride, e.g, e.wr, j0 + 1) * e.rs;
+    const RowStat st = epi_stat<AMK_OP_QKV>(e, L, u);
+    if (m.fmt == AMK_WEIGHTS_W8A16) {
+      y0 *= st.a;
+      y1 *= st.b;
     }
     int mat, head;
     unit_head(m, u, &mat, &head);
     const int i = u & (m.half - 1);
     if (mat != W_V) {
-      const float c = L.stat[g.nj + 2 * (u - t.begin)], s = L.stat[g.nj + 2 * (u - t.begin) + 1];
-      const float a = y0 * c - y1 * s;
-      const float b = y1 * c + y0 * s;
+      const float a = y0 * st.c - y1 * st.s;
+      const float b = y1 * st.c + y0 * st.s;
       y0 = a;
       y1 = b;
     }
@@ -805,39 +931,35 @@ __device__ __forceinline__ void epi_qkv(const DevModel& m, const amk_task_t& t, 
 
 // O and down projections: x_out = x_in + W y, with x_in rows taken from LDS
 // when this workgroup's previous residual task produced exactly those rows.
-__device__ __forceinline__ void epi_residual(const DevModel& m, const amk_task_t& t, const Gemv& g, const Lds& L,
-                                             Ctl& ctl, int lane) {
-  const int xin = t.op == AMK_OP_O ? 2 * t.layer : 2 * t.layer + 1;
-  const bool cached = ctl.res_buf == xin && ctl.res_lo == t.begin && ctl.res_hi == t.end;
-  const Ranges wr = wave_ranges(g);
-  for (int r = t.begin + lane; r < t.end; r += 64) {
-    float y = row_sum(L.part, m.part_stride, g, wr, r - t.begin);
-    if (g.int8) y *= L.stat[r - t.begin];
-    const float x = cached ? L.res[r - t.begin] : ldg<float>(m.x + (size_t)xin * m.xs + r);
+__device__ __forceinline__ void epi_residual(ModelRef m, const Epi& e, Res& res, int op, const Lds& L, int lane) {
+  const int xin = op == AMK_OP_O ? 2 * e.layer : 2 * e.layer + 1;
+  const bool cached = res.buf == xin && res.lo == e.begin && res.hi == e.end;
+  for (int r = e.begin + lane; r < e.end; r += 64) {
+    float y = row_sum(L.part, m.part_stride, e.g, e.wr, r - e.begin);
+    const RowStat st = epi_stat<AMK_OP_O>(e, L, r);
+    if (m.fmt == AMK_WEIGHTS_W8A16) y *= st.a;
+    const float x = xin == 0 ? st.c : cached ? L.res[r - e.begin] : ldg<float>(m.x + (size_t)xin * m.xs + r);
     const float o = x + y;
     stc(m.x + (size_t)(xin + 1) * m.xs + r, o);
-    L.res[r - t.begin] = o;
+    L.res[r - e.begin] = o;
   }
-  if (lane == 0) {
-    ctl.res_buf = xin + 1;
-    ctl.res_lo = t.begin;
-    ctl.res_hi = t.end;
-  }
+  res.buf = xin + 1;
+  res.lo = e.begin;
+  res.hi = e.end;
 }
 
-__device__ __forceinline__ void epi_gateup(const DevModel& m, const amk_task_t& t, const Gemv& g, const Lds& L,
-                                           float rs, int lane) {
-  const Ranges wr = wave_ranges(g);
-  for (int r = t.begin + lane; r < t.end; r += 64) {
-    const int j = 2 * (r - t.begin);
-    float gv = row_sum(L.part, m.part_stride, g, wr, j) * rs;
-    float uv = row_sum(L.part, m.part_stride, g, wr, j + 1) * rs;
-    if (g.int8) {
-      gv *= L.stat[j];
-      uv *= L.stat[j + 1];
+__device__ __forceinline__ void epi_gateup(ModelRef m, const Epi& e, const Lds& L, int lane) {
+  for (int r = e.begin + lane; r < e.end; r += 64) {
+    const int j = 2 * (r - e.begin);
+    float gv = row_sum(L.part, m.part_stride, e.g, e.wr, j) * e.rs;
+    float uv = row_sum(L.part, m.part_stride, e.g, e.wr, j + 1) * e.rs;
+    if (m.fmt == AMK_WEIGHTS_W8A16) {
+      const RowStat st = epi_stat<AMK_OP_GATEUP>(e, L, r);
+      gv *= st.a;
+      uv *= st.b;
     }
     const float silu = gv / (1.0f + __expf(-gv));
-    stc(m.a + (size_t)t.layer * m.as + r, silu * uv);
+    stc(m.a + (size_t)e.layer * m.as + r, silu * uv);
   }
 }
 
@@ -845,15 +967,13 @@ __device__ __forceinline__ void epi_gateup(const DevModel& m, const amk_task_t& 
 // logit never wins a comparison; it records the sticky status
 // AMK_ERR_NONFINITE, so the step's next token is reported as meaningless
 // instead of silently skipping it.
-__device__ __forceinline__ void epi_lmhead(const DevModel& m, const amk_task_t& t, const Gemv& g, const Lds& L,
-                                           float rs, float* logits, int lane) {
+__device__ __forceinline__ void epi_lmhead(ModelRef m, const Epi& e, const Lds& L, float* logits, int lane) {
   float best = -INFINITY;
   int besti = 0x7fffffff;
   bool nan = false;
-  const Ranges wr = wave_ranges(g);
-  for (int r = t.begin + lane; r < t.end; r += 64) {
-    float y = row_sum(L.part, m.part_stride, g, wr, r - t.begin) * rs;
-    if (g.int8) y *= L.stat[r - t.begin];
+  for (int r = e.begin + lane; r < e.end; r += 64) {
+    float y = row_sum(L.part, m.part_stride, e.g, e.wr, r - e.begin) * e.rs;
+    if (m.lm_fmt == AMK_WEIGHTS_W8A16) y *= epi_stat<AMK_OP_LMHEAD>(e, L, r).a;
     stc(logits + r, y);
     nan |= y != y;
     if (y > best || (y == best && r < besti)) { best = y; besti = r; }
@@ -866,13 +986,113 @@ __device__ __forceinline__ void epi_lmhead(const DevModel& m, const amk_task_t& 
     const int oi = __shfl_xor(besti, o);
     if (ob > best || (ob == best && oi < besti)) { best = ob; besti = oi; }
   }
-  if (lane == 0) stc(reinterpret_cast<float2*>(m.argp + 2 * t.aux), make_float2(best, __int_as_float(besti)));
+  if (lane == 0) stc(reinterpret_cast<float2*>(m.argp + 2 * e.aux), make_float2(best, __int_as_float(besti)));
 }
 
-__device__ __forceinline__ void argmax_final(const DevModel& m, const amk_task_t& t, int lane) {
+// Epilogue of a task of at most 64 items, one item per lane, in two halves.
+// Everything that does not need the row sums (addresses, which waves' partials
+// count, factors) is prepared by the last streaming wave while the task before
+// it is handed over, and left in ctl.prep; after B2, on the path every consumer
+// waits for, the sync wave only sums the partials, scales and stores.  (In one
+// piece on the sync wave the epilogue took 0.65-0.85 us of a 4.2 us stage of
+// the tiny decoder, 0.35 so.)
+struct Fast {
+  float f0, f1;      // int8 scales (1 otherwise)
+  float c, s;        // RoPE factors, or the layer-0 residual in c
+  uint64_t d0;       // where the (first) result goes, then
+  uint32_t d1;       // the second one's distance in bytes
+  uint32_t bits;     // 7 bits of waves whose partial of the first row counts, 7 of the second's, then:
+  enum { WIDE = 1 << 14, ROT = 1 << 15 };  // fp32 result (appended K / V: bf16); RoPE applies (q and K)
+};
+static_assert(sizeof(Fast) == 32, "two float4s");
+
+__device__ __forceinline__ uint32_t row_bits(const Gemv& g, const Ranges& wr, int j) {
+  const int lo = j * g.gpr, hi = lo + g.gpr;
+  uint32_t b = 0;
+#pragma unroll
+  for (int sw = 0; sw < NSW; ++sw) b |= max(wr.b[sw], lo) < min(wr.b[sw + 1], hi) ? 1u << sw : 0u;
+  return b;
+}
+
+__device__ __forceinline__ Fast fast_prepare(ModelRef m, const Ctl& ctl, const amk_task_t& t, int op, const RowStat& st,
+                                             int pos, uint16_t* kv, int lane) {
+  Fast f;
+  const int layer = uni(t.layer), begin = uni(t.begin), n = uni(t.end) - begin;
+  const int i = begin + min(lane, n - 1);
+  const bool pair = op == AMK_OP_QKV || op == AMK_OP_GATEUP;
+  const Gemv g = gemv_geom(ctl, op, n);
+  const Ranges wr = wave_ranges(g);
+  f.bits = row_bits(g, wr, pair ? 2 * lane : lane);
+  if (pair) f.bits |= row_bits(g, wr, 2 * lane + 1) << NSW;
+  const bool int8 = m.fmt == AMK_WEIGHTS_W8A16;
+  f.f0 = int8 ? st.a : 1.f;
+  f.f1 = int8 ? st.b : 1.f;
+  f.c = st.c;
+  f.s = st.s;
+  f.d1 = 0;
+  if (op == AMK_OP_QKV) {
+    int mat, head;
+    unit_head(m, i, &mat, &head);
+    const int k = i & (m.half - 1);
+    if (mat != W_V) f.bits |= Fast::ROT;
+    if (mat == W_Q) {
+      f.bits |= Fast::WIDE;
+      f.d0 = (uint64_t)(m.q + (size_t)layer * m.qs + (size_t)head * m.hd + k);
+      f.d1 = (uint32_t)m.half * 4;
+    } else {
+      f.d0 = (uint64_t)(kv + (((size_t)(layer * 2 + (mat == W_K ? 0 : 1)) * m.nkv + head) * m.max_seq + pos) * m.hd + k);
+      f.d1 = (uint32_t)m.half * 2;
+    }
+  } else if (op == AMK_OP_GATEUP) {
+    f.d0 = (uint64_t)(m.a + (size_t)layer * m.as + i);
+  } else {
+    f.d0 = (uint64_t)(m.x + (size_t)(2 * layer + (op == AMK_OP_O ? 1 : 2)) * m.xs + i);
+  }
+  return f;
+}
+
+__device__ __forceinline__ float masked_sum(const float* part, int stride, uint32_t bits, int j) {
+  uint32_t v[NSW];
+#pragma unroll
+  for (int sw = 0; sw < NSW; ++sw) v[sw] = __float_as_uint(part[sw * stride + j]);
+  float s = 0.f;
+#pragma unroll
+  for (int sw = 0; sw < NSW; ++sw) s += __uint_as_float(v[sw] & (uint32_t)((int)(bits << (31 - sw)) >> 31));
+  return s;
+}
+
+__device__ __forceinline__ void fast_finish(int op, int n, const Fast& f, float rs, const Lds& L, int pstride,
+                                            int lane) {
+  if (lane >= n) return;
+  if (op == AMK_OP_QKV) {
+    const float y0 = masked_sum(L.part, pstride, f.bits, 2 * lane) * rs * f.f0;
+    const float y1 = masked_sum(L.part, pstride, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
+    const bool rot = f.bits & Fast::ROT;
+    const float a = rot ? y0 * f.c - y1 * f.s : y0;
+    const float b = rot ? y1 * f.c + y0 * f.s : y1;
+    if (f.bits & Fast::WIDE) {
+      stc((float*)f.d0, a);
+      stc((float*)(f.d0 + f.d1), b);
+    } else {
+      stc((uint16_t*)f.d0, f2bf(a));
+      stc((uint16_t*)(f.d0 + f.d1), f2bf(b));
+    }
+  } else if (op == AMK_OP_GATEUP) {
+    const float gv = masked_sum(L.part, pstride, f.bits, 2 * lane) * rs * f.f0;
+    const float uv = masked_sum(L.part, pstride, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
+    const float silu = gv / (1.0f + __expf(-gv));
+    stc((float*)f.d0, silu * uv);
+  } else {
+    const float o = f.c + masked_sum(L.part, pstride, f.bits, lane) * f.f0;
+    stc((float*)f.d0, o);
+    L.res[lane] = o;
+  }
+}
+
+__device__ __forceinline__ void argmax_final(ModelRef m, int begin, int end, int lane) {
   float best = -INFINITY;
   int besti = 0x7fffffff;
-  for (int s = t.begin + lane; s < t.end; s += 64) {
+  for (int s = begin + lane; s < end; s += 64) {
     const float2 vi = ldg<float2>(m.argp + 2 * s);
     const int i = __float_as_int(vi.y);
     if (vi.x > best || (vi.x == best && i < besti)) { best = vi.x; besti = i; }
@@ -888,42 +1108,32 @@ __device__ __forceinline__ void argmax_final(const DevModel& m, const amk_task_t
 
 // ---------------------------------------------------------------- attention (all 8 waves)
 // Geometry of the attention of one KV group, shared with the host's LDS
-// sizing.  HD: head dim; GM: largest query group handled; EPL: head dims per
-// lane (8 for groups <= 4, 4 for groups <= 8 to halve the accumulators); LPR
-// lanes cover one K/V row, RPW rows per wave-wide load; each lane holds KB K
-// rows and KB V rows per pass, so a pass of the workgroup covers RP rows with
-// all its loads in flight at once.
+// sizing.  HD: head dim; GM: largest query group handled.  A tile is 16 K/V
+// rows; a wave holds up to T tiles per pass with all their loads in flight, so
+// one pass of the workgroup covers T * 16 * NW rows (384 for groups of at
+// most four heads).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int HD, int GM>
 struct AttnGeom {
-  static constexpr int EPL = GM <= 4 ? 8 : 4;
-  static constexpr int LPR = HD / EPL;
-  static constexpr int RPW = 64 / LPR;
-  static constexpr int KB = 9;
-  static constexpr int SB = 3;  // most rows per lane per softmax update
-  static constexpr int RP = NW * RPW * KB;
+  static constexpr int T = GM == 4 ? 3 : HD == 64 ? 2 : 1;  // what the registers hold
+  static constexpr int HS = GM / 4;      // sets of four query heads
+  static constexpr int KL = HD / 32;     // 16-byte loads per lane of a K tile, and of a V tile
+  static constexpr int VR = 512 / HD;    // rows per V load
+  static constexpr int RP = T * 16 * NW;
   // LDS scratch (floats): per-wave accumulators red[NW][GM][HD] and running
-  // (max, sum) stat[NW][GM][2]; the split merge reuses the region
+  // (max, sum) stat[NW][GM][2]; a wave's softmax weights lie in its part of
+  // red until it stores its accumulators; the split merge reuses the region
   static constexpr int SCRATCH = NW * GM * HD + 2 * NW * GM;
   static constexpr int MERGE = GM * 64 + 4 * NT;
   static constexpr int LDS = SCRATCH > MERGE ? SCRATCH : MERGE;
-  static_assert(LPR >= 2 && LPR <= 32, "lanes per row");
+  static_assert(GM % 4 == 0 && T * 16 * GM <= GM * HD, "the weights of a pass fit a wave's part of red");
+  // floats of the queries' bf16 parts [3][group][HD] in the activation region
+  static constexpr int QPARTS = 3 * GM * HD / 2;
 };
 
-template <int EPL> struct RowVec;
-template <> struct RowVec<8> { uint4 v; };
-template <> struct RowVec<4> { uint2 v; };
-
-template <int EPL>
-__device__ __forceinline__ RowVec<EPL> load_row(const uint16_t* p) {
-  RowVec<EPL> r;
-  if constexpr (EPL == 8) r.v = ldg<uint4>(p); else r.v = ldg<uint2>(p);
-  return r;
-}
-template <int EPL>
-__device__ __forceinline__ float row_elem(const RowVec<EPL>& r, int e) {
-  uint32_t w;
-  if constexpr (EPL == 8) w = (e < 2) ? r.v.x : (e < 4) ? r.v.y : (e < 6) ? r.v.z : r.v.w;
-  else w = (e < 2) ? r.v.x : r.v.y;
+__device__ __forceinline__ float row_elem(const uint4& v, int e) {
+  const uint32_t w = e < 2 ? v.x : e < 4 ? v.y : e < 6 ? v.z : v.w;
   return (e & 1) ? bf_hi(w) : bf_lo(w);
 }
 
@@ -933,173 +1143,250 @@ __device__ __forceinline__ float row_elem(const RowVec<EPL>& r, int e) {
 // flash-decoding family this follows).  Every wave keeps its own running
 // max / sum / accumulators over the rows it loads (online softmax, no
 // barrier inside the position loop); the waves merge through LDS at the end.
-// The queries are stored pre-multiplied by log2(e) / sqrt(d), so scores and
+//
+// Scores on the matrix cores: a tile's 16 K rows are the A operand of
+// v_mfma_f32_16x16x32_bf16 as they lie in the cache (lane l: row l % 16, 16
+// bytes), the B operand holds four query heads, each fp32 query cut into three
+// bf16 parts of 8 significant bits in columns h, 4 + h and 8 + h (columns 12
+// to 15 are zero).  Cut by truncation the three parts add up to the fp32 value
+// exactly, and a product of two 8-bit significands is exact in fp32, so the
+// sums differ from fp32 products only in their order.  On the vector units
+// the scores took 24 of 39 instructions per row.
+// The queries are pre-multiplied by log2(e) / sqrt(d), so scores and
 // maxima are in log2 units and each softmax weight is one exp2: the same
-// weights as exp(q.k / sqrt(d) - max), up to fp32 rounding.
+// weights as exp(q.k / sqrt(d) - max), up to fp32 rounding.  The weights
+// stay fp32 (through LDS, where a V row's lanes read all heads at once).
 // `record`: store per head (m, l, unnormalised acc) at dst[h * (kPartHead +
 // d)], else the normalised output at dst[h * d].  Stores are issued by every
 // wave; the caller drains them.
 template <int HD, int GM>
-__device__ __forceinline__ void attention(const DevModel& m, int layer, int g, int j0, int j1,
-                                          const uint16_t* __restrict__ kv, float* __restrict__ qs,
-                                          float* __restrict__ scr, float* __restrict__ dst, bool record, int wave,
-                                          int lane) {
+__device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, int j1, const uint16_t* __restrict__ kv,
+                                          float* __restrict__ qs, float* __restrict__ scr, float* __restrict__ dst,
+                                          bool record, int wave, int lane) {
   using A = AttnGeom<HD, GM>;
-  constexpr int EPL = A::EPL, LPR = A::LPR, RPW = A::RPW, KB = A::KB, SB = A::SB, RP = A::RP;
-  static_assert(KB == 9 && SB == 3, "sub-batches of 3, 3, 2 and 1 row slots");
+  constexpr int T = A::T, HS = A::HS, KL = A::KL, VR = A::VR, RP = A::RP, LPR = HD / 8;
   const int G = m.group;
   const int n = j1 - j0;
-  const int sub = lane / LPR, c = lane % LPR;
+  const int col = lane & 15, quad = lane >> 4;
+  const int sub = lane / LPR, c = lane % LPR;  // V: row within a load, 8-dim block
   const size_t hs = (size_t)m.max_seq * HD;
-  const uint16_t* Kp = kv + ((size_t)(layer * 2 + 0) * m.nkv + g) * hs + (size_t)j0 * HD + c * EPL;
-  const uint16_t* Vp = kv + ((size_t)(layer * 2 + 1) * m.nkv + g) * hs + (size_t)j0 * HD + c * EPL;
-
-  float m_run[GM], l_run[GM], acc[GM][EPL];
-#pragma unroll
-  for (int h = 0; h < GM; ++h) {
-    m_run[h] = -INFINITY;
-    l_run[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[h][e] = 0.f;
-  }
-
-  // the group's roped queries (G * HD / 4 <= NT float4s) into LDS first: the
-  // threads that move them do so before issuing their rows, so the queries
-  // do not wait behind the K / V stream
-  static_assert(GM * HD / 4 <= NT, "one query vector per thread");
-  if ((int)threadIdx.x < G * HD / 4) {
-    const float* qsrc = m.q + (size_t)layer * m.qs + (size_t)g * G * HD;
-    const float c = m.attn_scale * 1.4426950408889634f;  // log2(e) / sqrt(d)
-    float4 qv = ldg<float4>(qsrc + 4 * threadIdx.x);
-    qv.x *= c; qv.y *= c; qv.z *= c; qv.w *= c;
-    *reinterpret_cast<float4*>(qs + 4 * threadIdx.x) = qv;
-  }
-  for (int p0 = 0; p0 < n; p0 += RP) {
-    // rows of this lane: r_k = p0 + (k * NW + wave) * RPW + sub.  Every load
-    // is issued (rows past the range re-read its first row, whose score is
-    // masked to -inf, so it weighs 0): the compiler then waits for each row
-    // alone instead of the whole batch.
-    RowVec<EPL> kr[KB], vr[KB];
-#pragma unroll
-    for (int k = 0; k < KB; ++k) {
-      const int r = p0 + (k * NW + wave) * RPW + sub;
-      if (r < n) {
-        kr[k] = load_row<EPL>(Kp + (size_t)r * HD);
-        vr[k] = load_row<EPL>(Vp + (size_t)r * HD);
-      } else {
-        kr[k] = load_row<EPL>(Kp);
-        vr[k] = load_row<EPL>(Vp);
-      }
-    }
-    if (p0 == 0) __syncthreads();
-    // rows in sub-batches of 3, 3, 2 and 1 slots: scores for every query
-    // head, then one online-softmax update per head and sub-batch.  A wave
-    // whose range ends after 8 slots skips the last one instead of scoring a
-    // fully masked slot.  The running max / sum
-    // belong to the lane's row group (LPR lanes sharing its rows), so no
-    // cross-lane maximum is needed inside the loop.
-#pragma unroll
-    for (int sb = 0; sb < 4; ++sb) {
-      const int kb = sb == 0 ? 0 : sb == 1 ? 3 : sb == 2 ? 6 : 8;
-      const int NB = sb < 2 ? 3 : sb == 2 ? 2 : 1;
-      if (p0 + (kb * NW + wave) * RPW >= n) break;  // no row of this wave from here on
-      float sc[GM][SB];
-      // per query head: its LDS values once, then the scores of the SB rows
-#pragma unroll
-      for (int h = 0; h < GM; ++h) {
-        if (h < G) {
-          float q[EPL];
-#pragma unroll
-          for (int e = 0; e < EPL; e += 4) {
-            const float4 q4 = *reinterpret_cast<const float4*>(qs + h * HD + c * EPL + e);
-            q[e] = q4.x; q[e + 1] = q4.y; q[e + 2] = q4.z; q[e + 3] = q4.w;
-          }
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            const int k = kb + j;
-            const int r = p0 + (k * NW + wave) * RPW + sub;
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) d = fmaf(row_elem<EPL>(kr[k], e), q[e], d);
-            d = group_sum<LPR>(d);
-            sc[h][j] = r < n ? d : -INFINITY;
-          }
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < GM; ++h) {
-        if (h < G) {
-          float mx = sc[h][0];
-#pragma unroll
-          for (int j = 1; j < NB; ++j) mx = fmaxf(mx, sc[h][j]);
-          const float m_new = fmaxf(m_run[h], mx);
-          // a row group that has seen no row keeps (-inf, 0, 0)
-          const float mref = m_new == -INFINITY ? 0.f : m_new;
-          const float alpha = __builtin_amdgcn_exp2f(m_run[h] - mref);
-          float ls = 0.f;
-#pragma unroll
-          for (int j = 0; j < NB; ++j) {
-            sc[h][j] = __builtin_amdgcn_exp2f(sc[h][j] - mref);
-            ls += sc[h][j];
-          }
-          l_run[h] = l_run[h] * alpha + ls;
-          m_run[h] = m_new;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[h][e] *= alpha;
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        float vf[EPL];
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) vf[e] = row_elem<EPL>(vr[kb + j], e);
-#pragma unroll
-        for (int h = 0; h < GM; ++h) {
-          if (h < G) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[h][e] = fmaf(sc[h][j], vf[e], acc[h][e]);
-          }
-        }
-      }
-    }
-  }
-
-  // per wave: sum the accumulators of its row groups; then merge the waves
+  // uniform bases and 32-bit byte offsets per lane
+  const uint8_t* Kp = (const uint8_t*)(kv + ((size_t)(layer * 2 + 0) * m.nkv + g) * hs + (size_t)j0 * HD);
+  const uint8_t* Vp = (const uint8_t*)(kv + ((size_t)(layer * 2 + 1) * m.nkv + g) * hs + (size_t)j0 * HD);
   float* red = scr;                   // [NW][GM][HD]
   float* stat = scr + NW * GM * HD;   // [NW][GM][2]
+  float* wts = red + wave * GM * HD;  // this wave's weights: [HS][T * 16 rows][4 heads]
+
+  float m_run[HS], l_run[HS], acc[GM][8];
+#pragma unroll
+  for (int s = 0; s < HS; ++s) {
+    m_run[s] = -INFINITY;
+    l_run[s] = 0.f;
+  }
+#pragma unroll
+  for (int h = 0; h < GM; ++h)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
+
+  const bool active = wave * 16 < n;  // this wave has rows
+  // a thread's queries (one or two of the group's G * HD), loaded ahead of the
+  // rows; each is cut once and its parts go to qs[part][G * HD] as bf16
+  const int tid = wave * 64 + lane;
+  const float* qp = m.q + (size_t)layer * m.qs + (size_t)(g * G) * HD;
+  const float qscale = m.attn_scale * 1.4426950408889634f;  // log2(e) / sqrt(d)
+  constexpr int QN = GM * HD > NT ? 2 : 1;
+  float qv[QN];
+#pragma unroll
+  for (int i = 0; i < QN; ++i) qv[i] = ldg<float>(qp + min(tid + i * NT, G * HD - 1));
+  bf16x8 qf[HS][KL];
+
+  for (int p0 = 0; p0 < n; p0 += RP) {
+    // tile t of this wave: rows p0 + (t * NW + wave) * 16 ..; rows past the
+    // range re-read its last row, whose weight is set to 0
+    uint4 kr[T][KL], vr[T][KL];
+    auto load_v = [&](int t, int tb) {
+#pragma unroll
+      for (int j = 0; j < KL; ++j) vr[t][j] = ldg<uint4>(Vp + (uint32_t)(min(tb + j * VR + sub, n - 1) * (2 * HD) + c * 16));
+    };
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int tb = p0 + (t * NW + wave) * 16;
+      if (tb < n) {
+        const uint32_t ko = (uint32_t)(min(tb + col, n - 1) * (2 * HD) + quad * 16);
+#pragma unroll
+        for (int kb = 0; kb < KL; ++kb) kr[t][kb] = ldg<uint4>(Kp + ko + kb * 64);
+        if (t == 0) load_v(t, tb);
+      }
+    }
+    if (p0 == 0) {
+      uint16_t* qb = reinterpret_cast<uint16_t*>(qs);
+#pragma unroll
+      for (int i = 0; i < QN; ++i) {
+        const float x = qv[i] * qscale;
+        const float y = x - __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+        const float z = y - __uint_as_float(__float_as_uint(y) & 0xffff0000u);
+        if (tid + i * NT < G * HD) {
+          qb[tid + i * NT] = (uint16_t)(__float_as_uint(x) >> 16);
+          qb[G * HD + tid + i * NT] = (uint16_t)(__float_as_uint(y) >> 16);
+          qb[2 * G * HD + tid + i * NT] = (uint16_t)(__float_as_uint(z) >> 16);
+        }
+      }
+      __syncthreads();
+      // column col: part col / 4 of head col % 4 of the set, dims kb * 32 +
+      // quad * 8 ..; no such part or head: zero
+#pragma unroll
+      for (int s = 0; s < HS; ++s) {
+        const int h = s * 4 + (col & 3), part = col >> 2;
+        const bool on = part < 3 && h < G;
+        const uint16_t* qf0 = qb + (on ? part * G + h : 0) * HD + quad * 8;
+#pragma unroll
+        for (int kb = 0; kb < KL; ++kb) {
+          const uint4 v = *reinterpret_cast<const uint4*>(qf0 + kb * 32);
+          qf[s][kb] = __builtin_bit_cast(bf16x8, make_uint4(on ? v.x : 0, on ? v.y : 0, on ? v.z : 0, on ? v.w : 0));
+        }
+      }
+    }
+    f32x4 sv[HS][T];
+    float mx[HS];
+#pragma unroll
+    for (int s = 0; s < HS; ++s) mx[s] = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int tb = p0 + (t * NW + wave) * 16;
+      if (tb < n) {
+#pragma unroll
+        for (int s = 0; s < HS; ++s) {
+          f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int kb = 0; kb < KL; ++kb)
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[t][kb]), qf[s][kb], d, 0, 0, 0);
+          // lane: column col, rows quad * 4 + i; add the parts' columns
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float v = d[i];
+            v += dpp<0x128>(v);  // row_ror:8
+            v += dpp<0x124>(v);  // row_ror:4
+            v = tb + quad * 4 + i < n ? v : -INFINITY;
+            sv[s][t][i] = v;
+            mx[s] = fmaxf(mx[s], v);
+          }
+        }
+      }
+    }
+    // the V rows past the first tile take the K rows' registers
+#pragma unroll
+    for (int t = 1; t < T; ++t)
+      if (p0 + (t * NW + wave) * 16 < n) load_v(t, p0 + (t * NW + wave) * 16);
+    // one online-softmax update per head (lane's head: col % 4 of the set)
+    float alpha[HS];
+#pragma unroll
+    for (int s = 0; s < HS; ++s) {
+      const float m_new = fmaxf(m_run[s], xor32_max(xor16_max(mx[s])));
+      // a wave that has seen no row keeps (-inf, 0, 0)
+      const float mref = m_new == -INFINITY ? 0.f : m_new;
+      alpha[s] = __builtin_amdgcn_exp2f(m_run[s] - mref);
+      float ls = 0.f;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        if (p0 + (t * NW + wave) * 16 < n) {
+          float w[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            w[i] = __builtin_amdgcn_exp2f(sv[s][t][i] - mref);
+            ls += w[i];
+          }
+          // the four columns of a head hold the same weights: column 4 i + h
+          // stores row quad * 4 + i, so the tile lies linear in lane order
+          const int i = col >> 2;
+          wts[(s * T + t) * 64 + lane] = i == 0 ? w[0] : i == 1 ? w[1] : i == 2 ? w[2] : w[3];
+        }
+      }
+      l_run[s] = l_run[s] * alpha[s] + ls;
+      m_run[s] = m_new;
+    }
+    if (p0 > 0) {
+#pragma unroll
+      for (int h = 0; h < GM; ++h) {
+        const float al = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(alpha[h / 4]), h & 3));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[h][e] *= al;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      if (p0 + (t * NW + wave) * 16 < n) {
+#pragma unroll
+        for (int j = 0; j < KL; ++j) {
+          float vf[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) vf[e] = row_elem(vr[t][j], e);
+#pragma unroll
+          for (int s = 0; s < HS; ++s) {
+            const float4 w = *reinterpret_cast<const float4*>(wts + (s * T + t) * 64 + (j * VR + sub) * 4);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              acc[4 * s][e] = fmaf(w.x, vf[e], acc[4 * s][e]);
+              acc[4 * s + 1][e] = fmaf(w.y, vf[e], acc[4 * s + 1][e]);
+              acc[4 * s + 2][e] = fmaf(w.z, vf[e], acc[4 * s + 2][e]);
+              acc[4 * s + 3][e] = fmaf(w.w, vf[e], acc[4 * s + 3][e]);
+            }
+          }
+        }
+      }
+    }
+  }
+
+  // per wave: sum the accumulators over the row groups, two registers to one
+  // at each exchange, which leaves dims c * 8 + 2 * quad + {0, 1} of every head
+  // to a lane; then merge the waves
+#pragma unroll
+  for (int s = 0; s < HS; ++s) l_run[s] = across_sum<16>(l_run[s]);
 #pragma unroll
   for (int h = 0; h < GM; ++h) {
     if (h < G) {
-      // merge the row groups of the wave: rescale each to the wave's max
-      const float M = across_max<LPR>(m_run[h]);
-      const float f = m_run[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[h] - M);
-      const float l = across_sum<LPR>(l_run[h] * f);
+      if (active) {
+        float v[4];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const float v = across_sum<LPR>(acc[h][e] * f);
-        if (sub == 0) red[(wave * GM + h) * HD + c * EPL + e] = v;
+        for (int e = 0; e < 8; ++e)
+          if constexpr (LPR == 8) acc[h][e] += dpp<0x128>(acc[h][e]);  // row_ror:8
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[h][e]), __float_as_uint(acc[h][e + 4]), false, false);
+          v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[e]), __float_as_uint(v[e + 2]), false, false);
+          v[e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        *reinterpret_cast<float2*>(red + (wave * GM + h) * HD + c * 8 + 2 * quad) = make_float2(v[0], v[1]);
       }
-      if (lane == 0) {
-        stat[(wave * GM + h) * 2] = M;
-        stat[(wave * GM + h) * 2 + 1] = l;
+      if (lane == (h & 3)) {
+        stat[(wave * GM + h) * 2] = m_run[h / 4];
+        stat[(wave * GM + h) * 2 + 1] = l_run[h / 4];
       }
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < G * HD; i += NT) {
+  for (int i = wave * 64 + lane; i < G * HD; i += NT) {
     const int h = i / HD, d = i - h * HD;
-    float M = -INFINITY;
+    float2 ml[NW];
+    float r[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) M = fmaxf(M, stat[(w * GM + h) * 2]);
+    for (int w = 0; w < NW; ++w) {
+      ml[w] = *reinterpret_cast<const float2*>(stat + (w * GM + h) * 2);
+      r[w] = red[(w * GM + h) * HD + d];
+    }
+    float M = ml[0].x;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[w].x);
     float l = 0.f, o = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float mw = stat[(w * GM + h) * 2];
-      if (mw != -INFINITY) {
-        const float f = __builtin_amdgcn_exp2f(mw - M);
-        l = fmaf(f, stat[(w * GM + h) * 2 + 1], l);
-        o = fmaf(f, red[(w * GM + h) * HD + d], o);
-      }
+      // a wave without rows left (-inf, 0) and no accumulators
+      const float f = __builtin_amdgcn_exp2f(ml[w].x - M);
+      l = fmaf(f, ml[w].y, l);
+      o = fmaf(f, ml[w].x == -INFINITY ? 0.f : r[w], o);
     }
     if (record) {
       float* rec = dst + h * (kPartHead + HD);
@@ -1119,7 +1406,7 @@ __device__ __forceinline__ void attention(const DevModel& m, int layer, int g, i
 // All q / K / V loads of a round go out before any arithmetic, once per KV
 // group; positions past pos re-read row pos (clamped, unused).
 template <int HD, int FMT>
-__device__ __forceinline__ void attention_all(const DevModel& m, int layer, int pos, const uint16_t* __restrict__ kv,
+__device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, const uint16_t* __restrict__ kv,
                                               float* __restrict__ act, float* __restrict__ xsum, int wave,
                                               int lane) {
   constexpr int DPL = HD / 64;
@@ -1212,7 +1499,7 @@ __device__ __forceinline__ void attention_all(const DevModel& m, int layer, int 
 
 // Number of position splits with work at `pos` (split s covers positions
 // [s * chunk, (s + 1) * chunk) of 0..pos).
-__device__ __forceinline__ int active_splits(const DevModel& m, int pos, int* chunk_out) {
+__device__ __forceinline__ int active_splits(ModelRef m, int pos, int* chunk_out) {
   const int n_pos = pos + 1;
   const int chunk = (n_pos + m.nsplit - 1) / m.nsplit;
   if (chunk_out) *chunk_out = chunk;
@@ -1225,58 +1512,69 @@ __device__ __forceinline__ int active_splits(const DevModel& m, int pos, int* ch
 // float4 of the output over a share of the splits with all its loads in
 // flight, then the shares are added through LDS.
 template <int HD, int GM>
-__device__ __forceinline__ void merge_splits(const DevModel& m, int layer, int g, int S, float* scr, int wave,
+__device__ __forceinline__ void merge_splits(ModelRef m, int layer, int g, int S, float* scr, int wave,
                                              int lane) {
   const int G = m.group;
   const int rec = G * (kPartHead + HD);
   const float* base = m.part + (size_t)layer * m.ps + (size_t)g * m.nsplit * rec;
   float* wts = scr;                                        // [GM][64]
   float4* red = reinterpret_cast<float4*>(scr + GM * 64);  // [SP][E4]
+  const int E4 = G * HD / 4;                               // float4s of output
+  const int t = wave * 64 + lane;
+  // NT / E4 threads share an output: sp'th share of the splits
+  constexpr int SPMAX = 4 * NT / HD;
+  int SP = 1;
+#pragma unroll
+  for (int k = 2; k <= SPMAX; ++k)
+    if (k * E4 <= NT) SP = k;
+  int sp = 0;
+#pragma unroll
+  for (int k = 1; k < SPMAX; ++k)
+    if (t >= k * E4) sp = k;
+  const int o4 = t - sp * E4;
+  const int h = (4 * o4) / HD, d = 4 * o4 - h * HD;
+  const float* src = base + h * (kPartHead + HD) + kPartHead + d;
+  const bool on = sp < SP && o4 < E4;
+  float2 ml = make_float2(-INFINITY, 0.f);
+  if (wave < G && lane < S) ml = ldg<float2>(base + (size_t)lane * rec + wave * (kPartHead + HD));
+  // the first accumulators travel together with the maxima
+  float4 v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int s = sp + k * SP;
+    v[k] = on && s < S ? ldg<float4>(src + (size_t)s * rec) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
   if (wave < G) {
-    const int h = wave;
-    float ms = -INFINITY, ls = 0.f;
-    if (lane < S) {
-      const float2 ml = ldg<float2>(base + (size_t)lane * rec + h * (kPartHead + HD));
-      ms = ml.x;
-      ls = ml.y;
-    }
-    const float M = wave_max(ms);
-    const float w = lane < S ? __expf(ms - M) : 0.f;
-    const float inv = 1.0f / wave_sum(w * ls);
-    wts[h * 64 + lane] = w * inv;
+    const float M = wave_max(ml.x);
+    const float w = lane < S ? __expf(ml.x - M) : 0.f;
+    const float inv = 1.0f / wave_sum(w * ml.y);
+    wts[wave * 64 + lane] = w * inv;
   }
   __syncthreads();
-  const int E4 = G * HD / 4;         // float4s of output
-  const int SP = max(1, NT / E4);    // split shares
-  const int t = threadIdx.x;
-  const int o4 = t % E4, sp = t / E4;
-  const int h = (4 * o4) / HD, d = 4 * o4 - h * HD;
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (sp < SP) {
-    const float* src = base + h * (kPartHead + HD) + kPartHead + d;
-    for (int s0 = sp; s0 < S; s0 += 8 * SP) {
-      float4 v[8];
+  for (int s0 = sp;;) {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int s = s0 + k * SP;
-        v[k] = s < S ? ldg<float4>(src + (size_t)s * rec) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const int s = s0 + k * SP;
-        const float w = s < S ? wts[h * 64 + s] : 0.f;
-        a.x = fmaf(w, v[k].x, a.x); a.y = fmaf(w, v[k].y, a.y);
-        a.z = fmaf(w, v[k].z, a.z); a.w = fmaf(w, v[k].w, a.w);
-      }
+    for (int k = 0; k < 8; ++k) {
+      const int s = s0 + k * SP;
+      const float w = s < S ? wts[h * 64 + s] : 0.f;
+      a.x = fmaf(w, v[k].x, a.x); a.y = fmaf(w, v[k].y, a.y);
+      a.z = fmaf(w, v[k].z, a.z); a.w = fmaf(w, v[k].w, a.w);
     }
-    red[sp * E4 + o4] = a;
+    s0 += 8 * SP;
+    if (s0 >= S) break;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int s = s0 + k * SP;
+      v[k] = on && s < S ? ldg<float4>(src + (size_t)s * rec) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
   }
+  if (on) red[sp * E4 + o4] = a;
   __syncthreads();
   if (t < E4) {
     float4 o = red[t];
     for (int k = 1; k < SP; ++k) {
-      const float4 v = red[k * E4 + t];
-      o.x += v.x; o.y += v.y; o.z += v.z; o.w += v.w;
+      const float4 w = red[k * E4 + t];
+      o.x += w.x; o.y += w.y; o.z += w.z; o.w += w.w;
     }
     float* od = m.o + (size_t)layer * m.qs + (size_t)g * G * HD + 4 * t;
     stc(od, o.x); stc(od + 1, o.y); stc(od + 2, o.z); stc(od + 3, o.w);
@@ -1296,214 +1594,348 @@ __device__ __forceinline__ void merge_splits(const DevModel& m, int layer, int g
 // does not depend on the code size of the others.
 template <int HD, int GM, int FMT, bool TINY>
 __global__ void __launch_bounds__(NT, 1) __attribute__((aligned(65536)))
-amk_decode_kernel(DevModel m, int32_t token, int32_t pos, uint32_t epoch, uint16_t* __restrict__ kv,
+amk_decode_kernel(DevModel model, int32_t token, int32_t pos, uint32_t epoch, uint16_t* __restrict__ kv,
                   float* __restrict__ logits, uint64_t timeout_ticks) {
-  constexpr int PIPE = Pipe<FMT>::N;
+  constexpr int R = Ring<FMT>::R;
   extern __shared__ float4 lds4[];
   __shared__ Ctl ctl;
+  const AMK_CONST DevModel* mp = (const AMK_CONST DevModel*)__builtin_amdgcn_kernarg_segment_ptr();  // `model`
   Lds L;
   L.act = reinterpret_cast<float*>(lds4);
-  L.stat = L.act + m.lds_act;
-  L.res = L.stat + 2 * m.part_stride;
-  L.part = L.res + m.part_stride;
-  L.xsum = L.part + m.lds_scr;
+  L.stat = L.act + mp->lds_act;
+  L.res = L.stat + mp->lds_stat;
+  L.part = L.res + mp->lds_res;
+  L.xsum = L.part + mp->lds_scr;
 
   const int wave = uni(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int pstride = m.part_stride;
+  int lane = threadIdx.x & 63;
+  const int sw = wave - 1;
+  const uint64_t deadline = wall_clock64() + timeout_ticks;  // on this workgroup's clock from its start
+  uint64_t* const trace = mp->trace;
 
-  for (int i = threadIdx.x; i < m.lds_act; i += NT) L.act[i] = 0.f;
+  const int qb = ldc<int32_t>(mp->queue_start + blockIdx.x), qe = ldc<int32_t>(mp->queue_start + blockIdx.x + 1);
+  if (qb >= qe) return;
+
+  // ---- records, layer pointers and static data, staged ahead in LDS by the
+  // last streaming wave: dword `lane` of a record in lanes 0..15, dword
+  // `lane - 16` of a layer entry in lanes 16..47
+  typedef uint32_t __attribute__((may_alias)) dword;  // the records are read back as their own types
+  auto slot_dw = [&](int k) { return reinterpret_cast<dword*>(&ctl.slot[k & (NSLOT - 1)]); };
+  auto rec_dw = [&](int idx) { return (const uint32_t*)(mp->tasks + min(idx, qe - 1)); };
+  auto stat_for = [&](int idx) {  // static data of this lane's item of task idx
+    const Slot& sl = ctl.slot[idx & (NSLOT - 1)];
+    const int op = uni(sl.t.op), begin = uni(sl.t.begin), n = uni(sl.t.end) - begin;
+    RowStat r;
+    if (is_gemv(op) && n <= 64 && lane < n)
+      r = row_stat(*mp, sl, op, FMT == AMK_WEIGHTS_W8A16 && uni(ctl.geom[op].quant), begin + lane, token, pos);
+    return r;
+  };
+  auto prepare = [&](int idx, const RowStat& r) {  // the epilogue of task idx
+    const amk_task_t& t = ctl.slot[idx & (NSLOT - 1)].t;
+    const int op = uni(t.op);
+    if (!is_gemv(op) || op == AMK_OP_LMHEAD || uni(t.end) - uni(t.begin) > 64) return;
+    const Fast f = fast_prepare(*mp, ctl, t, op, r, pos, kv, lane);
+    ctl.prep[0][lane] = make_float4(f.f0, f.f1, f.c, f.s);
+    ctl.prep[1][lane] = make_float4(__uint_as_float((uint32_t)f.d0), __uint_as_float((uint32_t)(f.d0 >> 32)),
+                                    __uint_as_float(f.d1), __uint_as_float(f.bits));
+  };
+  uint32_t stage = 0;  // staging wave: a dword of record idx + 3 or layer idx + 2
+  RowStat nst;         // and static data of task idx + 1
+  auto stage_load = [&](int idx) {  // record idx, layer idx - 1
+    const uint32_t* lp = (const uint32_t*)(mp->layers + uni(ctl.slot[(idx - 1) & (NSLOT - 1)].t.layer));
+    stage = ldg<uint32_t>(lane < 16 ? rec_dw(idx) + lane : lp + min(lane - 16, 31));
+  };
+  if (wave == 1) {
+    constexpr int N = sizeof(ctl.geom) / 4;
+    static_assert(N <= 64, "one dword per lane");
+    if (lane < N) reinterpret_cast<dword*>(ctl.geom)[lane] = ldg<uint32_t>((const uint32_t*)mp->geom + lane);
+  } else if (wave == NW - 1) {
+    // the first three records (48 lanes), then the layers of the first two
+    if (lane < 48) slot_dw(qb + (lane >> 4))[lane & 15] = ldg<uint32_t>(rec_dw(qb + (lane >> 4)) + (lane & 15));
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    const int k = qb + (lane >> 5);
+    const uint32_t* lp = (const uint32_t*)(mp->layers + ctl.slot[k & (NSLOT - 1)].t.layer);
+    slot_dw(k)[16 + (lane & 31)] = ldg<uint32_t>(lp + (lane & 31));
+  }
+  for (int i = threadIdx.x; i < mp->lds_act; i += NT) L.act[i] = 0.f;
   if (threadIdx.x == 0) {
     ctl.abort = 0;
     ctl.cont = 0;
-    ctl.res_buf = -1;
-    ctl.res_lo = ctl.res_hi = 0;
   }
-
-  const int qb = ldc<int32_t>(m.queue_start + blockIdx.x), qe = ldc<int32_t>(m.queue_start + blockIdx.x + 1);
-  // streaming state carried from one task to the next (the weight loads of
-  // task idx are issued at the end of task idx - 1)
-  uint4 bufA[PIPE], bufB[PIPE];
-  uint32_t scA[PIPE], scB[PIPE];  // W4A16 group scales (unused otherwise)
-  Cursor ic;
-  int gi = 0, g0 = 0, g1 = 0;
-
-  auto prefetch = [&](int idx) {
-    g0 = g1 = gi = 0;
-    // redefined on every path, so the buffers are dead between a consumer
-    // and the next prefetch (attention and inline tasks reuse the registers)
-#pragma unroll
-    for (int i = 0; i < PIPE; ++i) {
-      bufA[i] = bufB[i] = make_uint4(0, 0, 0, 0);
-      scA[i] = scB[i] = 0;
-    }
-    if (idx >= qe) return;
-    const amk_task_t tn = ldc<amk_task_t>(m.tasks + idx);
-    if (!is_gemv(tn.op)) return;
-    const Gemv gn = gemv_geom(m, tn);
-    const int sw = wave - 1;
-    g0 = wave_gbegin(gn.G, sw);
-    g1 = wave_gbegin(gn.G, sw + 1);
-    gi = g0;
-    if (g0 < g1) {
-      cursor_init<FMT>(ic, m, tn, gn, g0);
-      issue_block<FMT>(bufA, scA, ic, gi, g1, m, tn, gn, lane);
-      issue_block<FMT>(bufB, scB, ic, gi, g1, m, tn, gn, lane);
-    }
-  };
-
-  // the step's deadline, on this workgroup's clock from its start
-  const uint64_t deadline = wall_clock64() + timeout_ticks;
-  if (qb < qe && wave != 0) prefetch(qb);
   __syncthreads();
 
-  for (int idx = qb; idx < qe; ++idx) {
-    const amk_task_t t = ldc<amk_task_t>(m.tasks + idx);
-    const bool gemv = is_gemv(t.op);
-    Gemv g;
-    if (gemv) g = gemv_geom(m, t);
-    uint64_t* tr = m.trace ? m.trace + (size_t)idx * AMK_TRACE_FIELDS : nullptr;
+  // ---- a streaming wave's ring of granules, its issue side, and the task
+  // whose first granules the ring holds
+  uint4 buf[R] = {};
+  uint32_t sc[R] = {};  // W4A16 group scales (unused otherwise)
+  Stream is;
+  int ring = -1, nj = 0, nc = 0, nn = 0;  // first job, granule and count of the wave's range in task `ring`
+  auto ring_begin = [&](int idx) {
+    stream_begin<FMT>(is, *mp, ctl, idx & (NSLOT - 1), sw, &nj, &nc);
+    nn = is.left;
+    ring = idx;
+  };
+  // empties the ring; called where its registers serve attention tasks, which
+  // also tells the compiler that they are free there
+  auto ring_drop = [&]() {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      buf[k] = make_uint4(0, 0, 0, 0);
+      sc[k] = 0;
+    }
+    ring = -1;
+  };
+  // fills an empty ring: a range shorter than the ring loads only what it has
+  // (the loads are waited for together with the input that follows them)
+  auto ring_fill = [&]() {
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+      if (is.left > 0) stream_issue<FMT>(is, buf[k], sc[k], *mp, ctl, lane);
+  };
 
-    // ---- B1a: the sync wave's counter wait
+  Poll poll;  // sync wave: the wait of the task to come
+  Res res;
+  if (wave == 0) {
+    poll = poll_for(*mp, ctl.slot[qb & (NSLOT - 1)].t, epoch, lane);
+  } else if (wave == NW - 1) {
+    prepare(qb, stat_for(qb));
+    nst = stat_for(qb + 1);
+    stage_load(qb + 3);
+  }
+
+  for (int idx = qb; idx < qe; ++idx) {
+    mp = reopen(mp);
+    asm volatile("" : "+v"(lane));  // nor is what follows from the lane kept in registers over all tasks
+    ModelRef m = *mp;
+    const Slot& sl = ctl.slot[idx & (NSLOT - 1)];
+    uint64_t* tr = trace ? trace + (size_t)idx * AMK_TRACE_FIELDS : nullptr;
+
+    // ---- B1a: the sync wave's counter wait; meanwhile the other waves load
+    // what depends on nothing: the task's first weights, unless the ring holds
+    // them already, and the gains of a normed input
+    bool ok = true;
     if (wave == 0) {
       if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_WAIT_BEGIN, (uint64_t)wall_clock64());
-      const bool ok = wait_deps<FMT>(m, t, m.tasks + idx, epoch, deadline, lane, tr);
+      ok = uni(wait_deps<FMT>(m, poll, deadline, lane, tr)) != 0;
       if (!ok && lane == 0) ctl.abort = 1;
       if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_WAIT_END, (uint64_t)wall_clock64());
     }
+    const int op = uni(sl.t.op), layer = uni(sl.t.layer), begin = uni(sl.t.begin), end = uni(sl.t.end);
+    const int aux = uni(sl.t.aux), chain = uni(sl.t.chain_counter);
+    const bool gemv = is_gemv(op);
+    const bool normed = is_normed(op);
+    const int next = idx + 1;
+    uint2 gv[NGAIN] = {};
+    const uint16_t *gain = nullptr, *src_bf = nullptr;
+    const float* src = nullptr;
+    int n4 = 0;
+    float* mypart = nullptr;
+    bool next_gemv = false;
+    if (wave != 0 && gemv) {
+      if (ring != idx) {
+        ring_begin(idx);
+        ring_fill();
+      }
+      if (normed) {
+        gain = op == AMK_OP_QKV ? unip(sl.ly.attn_norm) : op == AMK_OP_GATEUP ? unip(sl.ly.mlp_norm) : m.final_norm;
+        n4 = m.H >> 2;
+        load_gain(gain, n4, sw, lane, gv);
+        const int xi = op == AMK_OP_QKV ? 2 * layer : op == AMK_OP_GATEUP ? 2 * layer + 1 : 2 * m.L;
+        if (xi == 0) src_bf = m.embed + (size_t)token * m.H;
+        src = m.x + (size_t)xi * m.xs;
+      } else if (op == AMK_OP_DOWN) {
+        src = m.a + (size_t)layer * m.as;
+        n4 = m.I >> 2;
+      } else {
+        src = m.o + (size_t)layer * m.qs;
+        n4 = (m.nq * HD) >> 2;
+      }
+      mypart = L.part + sw * m.part_stride;
+      next_gemv = next < qe && is_gemv(uni(ctl.slot[next & (NSLOT - 1)].t.op));
+    }
     __syncthreads();
-    if (ctl.abort) return;
 
-    // an attention split with no positions at `pos` has no work
-    const bool attn = t.op == AMK_OP_ATTN;
-    int chunk = 0;
-    const int active = attn ? active_splits(m, pos, &chunk) : 0;
-    const bool idle = attn && t.begin >= active;
-
-    // ---- B1b: every wave moves its slice of the input activation
-    if (gemv) {
-      if constexpr (TINY) {
-        if (t.op == AMK_OP_O && t.aux == 1) attention_all<HD, FMT>(m, t.layer, pos, kv, L.act, L.xsum, wave, lane);
-        else load_input<FMT>(m, t, token, L, ctl, wave, lane);
-      } else {
-        load_input<FMT>(m, t, token, L, ctl, wave, lane);
-      }
-      __syncthreads();
-    }
-    if (tr && wave == 0 && lane == 0) stg<uint64_t>(tr + AMK_TRACE_INPUT_READY, (uint64_t)wall_clock64());
-
-    // ---- compute (the sync wave meanwhile fetches the epilogue's row data)
-    if (gemv && wave == 0) load_rowdata(m, t, token, pos, L, ctl, lane);
-    if (gemv && wave != 0 && g0 < g1) {
-      const int sw = wave - 1;
-      float* mypart = L.part + sw * pstride;
-      int cj = g0 / g.gpr, cc = g0 - cj * g.gpr, cg = g0;
-      float acc = 0.f;
-      constexpr int EX = Pipe<FMT>::EXTRA;
-      if constexpr (EX > 0) {
-        // blocks are consumed in the order they were issued: A, B, X[0], ...
-        uint4 bufX[EX][PIPE];
-        uint32_t scX[EX][PIPE];
-#pragma unroll
-        for (int b = 0; b < EX; ++b) issue_block<FMT>(bufX[b], scX[b], ic, gi, g1, m, t, g, lane);
-        while (cg < g1) {
-          consume_block<FMT>(bufA, scA, cj, cc, cg, g1, acc, L, mypart, g, lane);
-          issue_block<FMT>(bufA, scA, ic, gi, g1, m, t, g, lane);
-          consume_block<FMT>(bufB, scB, cj, cc, cg, g1, acc, L, mypart, g, lane);
-          issue_block<FMT>(bufB, scB, ic, gi, g1, m, t, g, lane);
-#pragma unroll
-          for (int b = 0; b < EX; ++b) {
-            consume_block<FMT>(bufX[b], scX[b], cj, cc, cg, g1, acc, L, mypart, g, lane);
-            issue_block<FMT>(bufX[b], scX[b], ic, gi, g1, m, t, g, lane);
-          }
-        }
-      } else {
-        while (cg < g1) {
-          consume_block<FMT>(bufA, scA, cj, cc, cg, g1, acc, L, mypart, g, lane);
-          issue_block<FMT>(bufA, scA, ic, gi, g1, m, t, g, lane);
-          consume_block<FMT>(bufB, scB, cj, cc, cg, g1, acc, L, mypart, g, lane);
-          issue_block<FMT>(bufB, scB, ic, gi, g1, m, t, g, lane);
-        }
-      }
-      if (cc != 0) {
-        const float s = wave_sum(acc);
-        if (lane == 0) mypart[cj] = s;
-      }
-    } else if constexpr (!TINY) {
-      if (attn && !idle) {
-        // one split: the normalised output directly; several: a partial record
-        const int j0 = t.begin * chunk, j1 = min(pos + 1, j0 + chunk);
-        const int rec = m.group * (kPartHead + HD);
-        float* dst = active == 1 ? m.o + (size_t)t.layer * m.qs + (size_t)t.aux * m.group * HD
-                                 : m.part + (size_t)t.layer * m.ps + ((size_t)t.aux * m.nsplit + t.begin) * rec;
-        attention<HD, GM>(m, t.layer, t.aux, j0, j1, kv, L.act, L.part, dst, active > 1, wave, lane);
-        drain_vmem();
-      }
-    }
-    __syncthreads();  // B2: GEMV partials in LDS, attention results stored
-    // W4A16 in the tiny-context kernel: the next task's weight loads go out now,
-    // while the sync wave publishes.  They delay this task's result stores in
-    // the CU's request queue, which measured slower for bf16 and int8 weights
-    // (+23 us per 8B step each) and faster for int4 (-34 us), whose tasks carry
-    // a quarter of bf16's bytes per row.
-    constexpr bool EARLY = TINY && FMT == AMK_WEIGHTS_W4A16;
-    if constexpr (EARLY) {
-      if (wave != 0) prefetch(idx + 1);
-    }
-
-    // ---- publish (sync wave)
+    uint32_t* sig = nullptr;
     if (wave == 0) {
-      if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_COMPUTE_END, (uint64_t)wall_clock64());
-      switch (t.op) {
-        case AMK_OP_QKV: epi_qkv(m, t, g, L, pos, kv, input_rs(m, ctl), lane); break;
-        case AMK_OP_O: case AMK_OP_DOWN: epi_residual(m, t, g, L, ctl, lane); break;
-        case AMK_OP_GATEUP: epi_gateup(m, t, g, L, input_rs(m, ctl), lane); break;
-        case AMK_OP_LMHEAD: epi_lmhead(m, t, g, L, input_rs(m, ctl), logits, lane); break;
-        case AMK_OP_ARGMAX: argmax_final(m, t, lane); break;
-        default: break;
-      }
-      if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_PUBLISHED, (uint64_t)wall_clock64());
-      bool cont = false;
-      if (t.chain_counter >= 0) {
+      sig = counter_copy(m, uni(sl.t.signal_counter), lane);
+      if (next < qe) poll = poll_for(m, ctl.slot[next & (NSLOT - 1)].t, epoch, lane);
+    }
+    // the attention scratch: behind the queries in the activation region (free
+    // then) where the partials region has no room for it
+    float* scr = m.scr_at ? L.act + m.scr_at : L.part;
+    int active = 0;  // attention splits with work at `pos`
+    auto traced = [&](int field) {
+      if (tr && wave == 0 && lane == 0) stg<uint64_t>(tr + field, (uint64_t)wall_clock64());
+    };
+    auto publish = [&]() {  // sync wave: results stored
+      traced(AMK_TRACE_PUBLISHED);
+      if (chain >= 0) {
         // the producer that completes the counter runs its inline task: a QKV
         // task's group has npg producers, an attention split's nsplit
-        const uint32_t producers = t.op == AMK_OP_QKV ? (uint32_t)m.npg : (uint32_t)m.nsplit;
-        cont = release_signal_last(m, t.signal_counter, epoch * producers, lane);
+        const uint32_t producers = op == AMK_OP_QKV ? (uint32_t)m.npg : (uint32_t)m.nsplit;
+        const bool cont = release_signal_last(sig, epoch * producers);
         if (cont) acquire_after_poll();
+        if (lane == 0) ctl.cont = cont;
       } else {
-        release_signal(m, t.signal_counter, lane);
+        release_signal(sig);
       }
-      if (lane == 0) ctl.cont = cont;
-      if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_SIGNALLED, (uint64_t)wall_clock64());
+      traced(AMK_TRACE_SIGNALLED);
+      if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_CHAINED, 0ull);
+    };
+
+    if (gemv) {
+      // ---- B1b: the input activation; the sync wave prepares the epilogue
+      Epi e;
+      Fast f;
+      float rs = 1.f;
+      const bool small = end - begin <= 64 && op != AMK_OP_LMHEAD;
+      if (wave != 0) {
+        if (normed) load_input_normed<FMT>(src, src_bf, gain, n4, gv, L, ctl, sw, lane);
+        else if (!TINY || op == AMK_OP_DOWN) load_input<FMT>(src, n4, L, sw, lane);
+      }
+      if constexpr (TINY) {
+        if (op == AMK_OP_O) attention_all<HD, FMT>(m, layer, pos, kv, L.act, L.xsum, wave, lane);
+      }
+      if (wave == 0) {
+        if (small) {
+          const float4 a = ctl.prep[0][lane], b = ctl.prep[1][lane];
+          f.f0 = a.x; f.f1 = a.y; f.c = a.z; f.s = a.w;
+          f.d0 = (uint64_t)__float_as_uint(b.y) << 32 | __float_as_uint(b.x);
+          f.d1 = __float_as_uint(b.z);
+          f.bits = __float_as_uint(b.w);
+          if (op == AMK_OP_O || op == AMK_OP_DOWN) {
+            const int xin = 2 * layer + (op == AMK_OP_DOWN);
+            if (xin != 0) {
+              if (res.buf == xin && res.lo == begin && res.hi == end) f.c = L.res[min(lane, end - begin - 1)];
+              else f.c = ldg<float>(m.x + (size_t)xin * m.xs + begin + min(lane, end - begin - 1));
+            }
+            res.buf = xin + 1;
+            res.lo = begin;
+            res.hi = end;
+          }
+        } else {
+          e.layer = layer; e.begin = begin; e.end = end; e.aux = aux;
+          e.g = gemv_geom(ctl, op, end - begin);
+          e.wr = wave_ranges(e.g);
+        }
+      }
+      __syncthreads();
+      traced(AMK_TRACE_INPUT_READY);
+
+      // ---- compute
+      bool fill = false;  // the ring takes the next task's granules after B2
+      if (wave == 0) {
+        if (normed) rs = input_rs(m, ctl);
+        if (!small) {
+          e.rs = rs;
+          for (int i = begin + lane; i < end; i += 64)
+            put_stat(L, op, i - begin, row_stat(m, sl, op, FMT == AMK_WEIGHTS_W8A16 && e.g.quant, i, token, pos));
+        }
+      } else {
+        Work w;
+        w.j = nj; w.c = nc; w.left = nn;
+        w.gpr = is.gpr; w.lastb = is.lastb; w.quant = is.quant;
+        // blocks of R granules; the last one of several already refills the
+        // ring with the next task's granules
+        const int nblk = max(1, (nn + R - 1) / R);
+        fill = next_gemv && nblk == 1;
+        const int full = next_gemv && nblk > 1 ? nblk : nblk - 1;
+        for (int b = 0; b < full; ++b) {
+          if (b == nblk - 1) ring_begin(next);
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            consume<FMT>(w, buf[k], sc[k], L, mypart, lane);
+            stream_issue<FMT>(is, buf[k], sc[k], m, ctl, lane);
+          }
+        }
+        if (full < nblk) {
+#pragma unroll
+          for (int k = 0; k < R; ++k) consume<FMT>(w, buf[k], sc[k], L, mypart, lane);
+        }
+        if (w.c != 0) {
+          const float r = wave_sum(w.acc);
+          if (lane == 0) mypart[w.j] = r;
+        }
+      }
+      const int pstride = m.part_stride;
+      __syncthreads();  // B2: partials in LDS
+      traced(AMK_TRACE_COMPUTE_END);
+      if (wave == 0) {
+        if (!ok) return;
+        if (small) {
+          fast_finish(op, end - begin, f, rs, L, pstride, lane);
+        } else {
+          switch (op) {
+            case AMK_OP_QKV: epi_qkv(m, e, L, pos, kv, lane); break;
+            case AMK_OP_O: case AMK_OP_DOWN: epi_residual(m, e, res, op, L, lane); break;
+            case AMK_OP_GATEUP: epi_gateup(m, e, L, lane); break;
+            default: epi_lmhead(m, e, L, logits, lane); break;
+          }
+        }
+        publish();
+      } else {
+        if (uni(ctl.abort)) return;
+        if (fill) {
+          ring_begin(next);
+          ring_fill();
+        }
+      }
+    } else {
+      if (uni(ctl.abort)) return;
+      traced(AMK_TRACE_INPUT_READY);
+      if constexpr (!TINY) {
+        if (op == AMK_OP_ATTN) {
+          int chunk = 0;
+          active = active_splits(m, pos, &chunk);
+          // a split with no positions at `pos` has no work
+          if (begin < active) {
+            // one split: the normalised output directly; several: a partial record
+            const int j0 = begin * chunk, j1 = min(pos + 1, j0 + chunk);
+            const int rec = m.group * (kPartHead + HD);
+            float* dst = active == 1 ? m.o + (size_t)layer * m.qs + (size_t)aux * m.group * HD
+                                     : m.part + (size_t)layer * m.ps + ((size_t)aux * m.nsplit + begin) * rec;
+            attention<HD, GM>(m, layer, aux, j0, j1, kv, L.act, scr, dst, active > 1, wave, lane);
+            drain_vmem();
+          }
+          ring_drop();
+        }
+      }
+      __syncthreads();  // B2: attention results stored
+      traced(AMK_TRACE_COMPUTE_END);
+      if (wave == 0) {
+        if (op == AMK_OP_ARGMAX) argmax_final(m, begin, end, lane);
+        publish();
+      }
     }
-    __syncthreads();  // B3: results released and signalled
+    if (wave == NW - 1) {
+      // the staged dwords and static data arrive in LDS, the next ones set out
+      if (lane < 48) slot_dw(lane < 16 ? idx + 3 : idx + 2)[lane] = stage;
+      prepare(next, nst);
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      nst = stat_for(idx + 2);
+      stage_load(idx + 4);
+    }
 
     // ---- inline task of the chain counter (all waves; never in the tiny schedule)
     if constexpr (!TINY) {
-      if (ctl.cont) {
-        if (t.op == AMK_OP_QKV) {
-          float* dst = m.o + (size_t)t.layer * m.qs + (size_t)t.aux * m.group * HD;
-          attention<HD, GM>(m, t.layer, t.aux, 0, pos + 1, kv, L.act, L.part, dst, false, wave, lane);
-        } else if (active > 1) {
-          merge_splits<HD, GM>(m, t.layer, t.aux, active, L.part, wave, lane);
+      if (chain >= 0) {
+        __syncthreads();  // B3: results released and signalled
+        if (uni(ctl.cont)) {
+          if (op == AMK_OP_QKV) {
+            float* dst = m.o + (size_t)layer * m.qs + (size_t)aux * m.group * HD;
+            attention<HD, GM>(m, layer, aux, 0, pos + 1, kv, L.act, scr, dst, false, wave, lane);
+          } else if (active > 1) {
+            merge_splits<HD, GM>(m, layer, aux, active, scr, wave, lane);
+          }
+          ring_drop();
+          drain_vmem();
+          __syncthreads();  // B4: inline results stored
+          if (wave == 0) {
+            release_signal(counter_copy(m, chain, lane));
+            if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_CHAINED, (uint64_t)wall_clock64());
+          }
         }
-        drain_vmem();
-        __syncthreads();  // B4: inline results stored
-        if (wave == 0) {
-          release_signal(m, t.chain_counter, lane);
-          if (tr && lane == 0) stg<uint64_t>(tr + AMK_TRACE_CHAINED, (uint64_t)wall_clock64());
-        }
-        __syncthreads();  // B5: the next task's loads go out after the chain signal
-      } else if (tr && wave == 0 && lane == 0) {
-        stg<uint64_t>(tr + AMK_TRACE_CHAINED, 0ull);
       }
-    } else if (tr && wave == 0 && lane == 0) {
-      stg<uint64_t>(tr + AMK_TRACE_CHAINED, 0ull);
-    }
-
-    // ---- the next task's weight stream (streaming waves)
-    if constexpr (!EARLY) {
-      if (wave != 0) prefetch(idx + 1);
     }
   }
 }
@@ -1581,6 +2013,7 @@ static const void* kernel_for(int head_dim, int group, int fmt, bool tiny) {
 }
 
 extern "C" int amk_internal_threads(void) { return NT; }
+extern "C" int amk_internal_static_lds(void) { return (int)sizeof(Ctl); }
 
 // Floats of LDS scratch the attention and split merge of one task need (in
 // the partials region).
