@@ -531,6 +531,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     while ((1 << m.half_log2) < s.half) ++m.half_log2;
     m.units = s.units; m.q_units = s.q_units; m.nsplit = s.nsplit; m.n_lm = n_lm;
     m.gq2 = s.group + 2;
+    m.group_magic = s.group > 1 ? (uint32_t)(((1ull << 32) + s.group - 1) / s.group) : 0;
     m.gq2_magic = (uint32_t)(((1ull << 32) + m.gq2 - 1) / m.gq2);
     m.npg = s.npg;
     m.n_cu = n_cu;

@@ -51,6 +51,7 @@ struct DevModel {
   int32_t qglog2;     // W4A16: log2 of the input columns per scale
   int32_t group, half, half_log2, units, q_units, nsplit, n_lm;
   int32_t gq2;        // group + 2: head slots of one KV group in QKV unit order
+  uint32_t group_magic; // the same for group; 0 for group 1
   uint32_t gq2_magic; // ceil(2^32 / gq2): n / gq2 = mulhi(n, magic) for head slots
   int32_t npg;        // QKV tasks per KV group (producers of a group's QKV counter)
   int32_t n_cu;

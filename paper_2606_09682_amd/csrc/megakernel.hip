@@ -1397,7 +1397,7 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
 // computes it itself instead of waiting for an attention stage.  Each wave
 // takes HR heads per round; lane owns head dims [lane * DPL, (lane + 1) * DPL).
 // All q / K / V loads of a round go out before any arithmetic, once per KV
-// group; positions past pos re-read row pos (clamped, unused).
+// group.
 template <int HD, int FMT>
 __device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, const uint16_t* __restrict__ kv,
                                               float* __restrict__ act, float* __restrict__ xsum, int wave,
@@ -1409,14 +1409,16 @@ __device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, co
   const size_t hs = (size_t)m.max_seq * HD;
   // the HR heads of a round share one KV group when the group size is a
   // multiple of HR (heads h0.. h0 + HR - 1 with h0 a multiple of HR)
-  const bool one_group = m.group % HR == 0;
+  const int group = m.group;
+  const bool one_group = (group & (HR - 1)) == 0;
+  const float scale = m.attn_scale;
   for (int h0 = wave * HR; h0 < m.nq; h0 += NW * HR) {
     float qv[HR][DPL];
-    uint32_t kr[HR][T], vr[HR][T];  // DPL bf16 values per row (the low half only when DPL == 1)
+    uint32_t kr[HR][T] = {}, vr[HR][T] = {};  // DPL bf16 values per row (the low half only when DPL == 1)
 #pragma unroll
     for (int i = 0; i < HR; ++i) {
       const int h = min(h0 + i, m.nq - 1);
-      const int g = h / m.group;
+      const int g = (int)__umulhi((uint32_t)h, m.group_magic) + (group == 1 ? h : 0);  // h / group
       const float* qh = m.q + (size_t)layer * m.qs + (size_t)h * HD + lane * DPL;
       const uint16_t* Kp = kv + ((size_t)(layer * 2) * m.nkv + g) * hs + lane * DPL;
       const uint16_t* Vp = kv + ((size_t)(layer * 2 + 1) * m.nkv + g) * hs + lane * DPL;
@@ -1427,18 +1429,18 @@ __device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, co
       } else {
         qv[i][0] = ldg<float>(qh);
       }
-      // one load per KV group (the other heads of the group copy it below);
-      // positions past pos re-read row pos (clamped, unused)
+      // one load per KV group (the other heads of the group copy it below)
       if (i > 0 && one_group) continue;
 #pragma unroll
       for (int p = 0; p < T; ++p) {
-        const size_t off = (size_t)min(p, n - 1) * HD;
-        if constexpr (DPL == 2) {
-          kr[i][p] = ldg<uint32_t>(Kp + off);
-          vr[i][p] = ldg<uint32_t>(Vp + off);
-        } else {
-          kr[i][p] = ldg<uint16_t>(Kp + off);
-          vr[i][p] = ldg<uint16_t>(Vp + off);
+        if (p < n) {
+          if constexpr (DPL == 2) {
+            kr[i][p] = ldg<uint32_t>(Kp + p * HD);
+            vr[i][p] = ldg<uint32_t>(Vp + p * HD);
+          } else {
+            kr[i][p] = ldg<uint16_t>(Kp + p * HD);
+            vr[i][p] = ldg<uint16_t>(Vp + p * HD);
+          }
         }
       }
     }
@@ -1461,7 +1463,7 @@ __device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, co
         if (p < n) {
           float d = qv[i][0] * bf_lo(kr[i][p]);
           if constexpr (DPL == 2) d = fmaf(qv[i][1], bf_hi(kr[i][p]), d);
-          d = wave_sum(d) * m.attn_scale;
+          d = wave_sum(d) * scale;
           const float mn = fmaxf(mrun, d);
           const float alpha = __expf(mrun - mn), e = __expf(d - mn);
           l = l * alpha + e;
