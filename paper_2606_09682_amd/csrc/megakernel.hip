@@ -1182,6 +1182,11 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
     for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
 
   const bool active = wave * 16 < n;  // this wave has rows
+  // long splits stream their rows past the caches like the weights (Llama-3.2-1B
+  // W8A16 at position 4096, 129 rows a split: 689 us a step, 679 so); a short
+  // context is found in them again at the next step (SmolLM2 at position 200,
+  // one task of 201 rows a group: 677, and 692 with non-temporal loads)
+  const bool nt = record && n >= 96;
   // a thread's queries (one or two of the group's G * HD), loaded ahead of the
   // rows; each is cut once and its parts go to qs[part][G * HD] as bf16
   const int tid = wave * 64 + lane;
@@ -1199,7 +1204,10 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
     uint4 kr[T][KL], vr[T][KL];
     auto load_v = [&](int t, int tb) {
 #pragma unroll
-      for (int j = 0; j < KL; ++j) vr[t][j] = ldg<uint4>(Vp + (uint32_t)(min(tb + j * VR + sub, n - 1) * (2 * HD) + c * 16));
+      for (int j = 0; j < KL; ++j) {
+        const uint32_t vo = (uint32_t)(min(tb + j * VR + sub, n - 1) * (2 * HD) + c * 16);
+        vr[t][j] = nt ? ldnt<uint4>(Vp + vo) : ldg<uint4>(Vp + vo);
+      }
     };
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -1207,7 +1215,7 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
       if (tb < n) {
         const uint32_t ko = (uint32_t)(min(tb + col, n - 1) * (2 * HD) + quad * 16);
 #pragma unroll
-        for (int kb = 0; kb < KL; ++kb) kr[t][kb] = ldg<uint4>(Kp + ko + kb * 64);
+        for (int kb = 0; kb < KL; ++kb) kr[t][kb] = nt ? ldnt<uint4>(Kp + ko + kb * 64) : ldg<uint4>(Kp + ko + kb * 64);
         if (t == 0) load_v(t, tb);
       }
     }

@@ -1,0 +1,93 @@
+"""Edges of the decode kernel's tiles and hand-over, against the CPU oracle.
+
+Attention works on tiles of 16 K/V rows over eight waves, with one, two or
+three tiles per wave and pass (by head size and query group), and cuts every
+fp32 query into three bf16 parts; a wave's weight stream runs on from one task
+into the next, with rings shorter and longer than a task; a task's epilogue is
+prepared ahead for up to 64 items.  Bar: the greedy token, and logits within
+2e-4 of the largest logit.  All sums are fp32 (about 1e-6 of it each through
+two layers); what is left is an appended K / V element whose bf16 rounding the
+other order of summation flips (2^-8 of one element of one averaged row, so at
+most about 2^-8 / sqrt(64) of an attention output at position 0, less behind
+the residual stream and at later positions)."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+from synth.device import config_kwargs, kv_to_device, weights_to_device
+
+pytestmark = pytest.mark.gpu
+
+# name: heads, kv_heads, head_dim  (query groups 1, 3, 4, 5, 8 on both head sizes)
+HEADS = {"g1_64": (2, 2, 64), "g3_64": (6, 2, 64), "g8_64": (8, 1, 64), "g4_128": (4, 1, 128), "g5_128": (5, 1, 128),
+         "g8_128": (8, 1, 128)}
+
+
+def shape_of(heads, hidden=256, inter=320, vocab=1000, layers=2, tied=False):
+    nq, nkv, d = HEADS[heads]
+    return synth.get("tiny").with_(name=f"edge_{heads}_{hidden}_{inter}_{vocab}", hidden=hidden, n_layers=layers,
+                                   n_heads=nq, n_kv_heads=nkv, head_dim=d, intermediate=inter, vocab=vocab,
+                                   tied_embeddings=tied)
+
+
+def check(cfg, fmt, pos, tuning=None, group=0, steps=1):
+    import torch
+    from paper_2606_09682_amd import amk
+    w = synth.make_weights(cfg, seed=3)
+    if fmt == "w8a16":
+        synth.add_w8a16(w)
+    if fmt == "w4a16":
+        synth.add_w4a16(w, group=group)
+    kv = synth.make_kv_cache(cfg, pos, seed=1, max_seq=pos + steps)
+    dec = amk.Decoder(amk.make_config(**config_kwargs(cfg, fmt, pos + steps, group)), weights_to_device(w, fmt),
+                      amk.amk_tuning_t(*tuning) if tuning else None)
+    dkv = kv_to_device(kv)
+    logits = torch.empty((cfg.vocab + 3) // 4 * 4, dtype=torch.float32, device="cuda")
+    ref_kv = kv.copy()
+    model = oracle.OracleModel(w, fmt, np.float32)
+    tok = 1
+    for i in range(steps):
+        dec.step(tok, pos + i, dkv, logits)
+        got = dec.next_token()
+        ref = oracle.decode_step(model, tok, pos + i, ref_kv)
+        err = float(np.max(np.abs(logits.cpu().numpy()[:cfg.vocab] - ref)) / np.max(np.abs(ref)))
+        print(f"[edges] {cfg.name} {fmt} pos {pos + i}: relative logit error {err:.2e}", flush=True)
+        assert err <= (2e-4 if pos >= 8 else 5e-3)
+        assert got == oracle.argmax_first(ref)
+        tok = got
+    assert dec.status() == amk.AMK_OK
+    dec.close()
+
+
+@pytest.mark.parametrize("heads", list(HEADS))
+@pytest.mark.parametrize("pos", [14, 15, 16, 126, 128, 255, 256, 383, 384, 800])
+def test_attention_tile_edges(heads, pos):
+    """One task holds all rows of a KV group (short schedule): whole and partial
+    tiles, the last wave with a tile, one, two and more passes."""
+    check(shape_of(heads), "bf16", pos, tuning=(0, 0, 0, 0, 1 << 30, -1, 0))
+
+
+@pytest.mark.parametrize("heads", ["g3_64", "g8_64", "g4_128", "g8_128"])
+@pytest.mark.parametrize("splits,pos", [(2, 31), (3, 400), (64, 500), (7, 700), (1, 40)])
+def test_split_and_merge_edges(heads, splits, pos):
+    """Split records of ragged lengths and their merge (long schedule); splits
+    past the last row; rows loaded non-temporally (96 and more a split)."""
+    check(shape_of(heads), "bf16", pos, tuning=(splits, 0, 0, 0, -1, -1, 0))
+
+
+@pytest.mark.parametrize("fmt,group", [("bf16", 0), ("w8a16", 0), ("w4a16", 32), ("w4a16", 64)])
+@pytest.mark.parametrize("hidden,inter,vocab", [(256, 320, 40), (1088, 4160, 3001), (7232, 1088, 520)])
+def test_stream_and_epilogue_edges(fmt, group, hidden, inter, vocab):
+    """Ranges shorter and longer than the ring, short last granules, LM-head
+    tasks of one row and of several, and a hidden size whose RMSNorm gains do not
+    all fit a wave's preload; steps from position 0 (tiny, then short schedule)."""
+    check(shape_of("g3_64", hidden, inter, vocab), fmt, 0, group=group, steps=8)
+
+
+@pytest.mark.parametrize("rows", [2, 24, 64, 66, 130])
+@pytest.mark.parametrize("fmt", ["bf16", "w8a16"])
+def test_task_size_edges(fmt, rows):
+    """Row caps around the 64 items an epilogue is prepared for (a row pair is
+    one item): many small tasks a queue, and tasks on both sides of the line."""
+    check(shape_of("g4_128", 512, 17408 if rows > 64 else 2048, 20000), fmt, 20, tuning=(0, 0, rows, 0, 0, 0, 0))
