@@ -363,6 +363,15 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
       free_handle(h);
       return AMK_ERR_DEVICE;
     }
+    // the shapes taken are those whose activation leaves room for a task of the
+    // row cap: partials, two static values and a residual per row
+    const size_t cap = round_up((size_t)s.max_jobs, 4);
+    const size_t room = (act + act / 16 + 3 * cap + std::max((size_t)nsw * cap, attn) + xsum) * 4;
+    if ((long)room + 256 > (long)max_lds) {
+      std::fprintf(stderr, "amk: needs %zu B of LDS per workgroup, device allows %d\n", room, max_lds);
+      free_handle(h);
+      return AMK_ERR_UNSUPPORTED;
+    }
     if ((long)lds_bytes + amk_internal_static_lds() > (long)max_lds && qrows + attn <= act_lds) {
       scr_at = qrows;
       scr = (size_t)nsw * pstride;

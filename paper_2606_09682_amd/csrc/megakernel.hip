@@ -10,12 +10,13 @@
 //               int8 row scale, argmax), writes every result other CUs read,
 //               then releases and signals.
 //   waves 1..7  "streaming waves": stream the task's weight rows from HBM in
-//               16-byte-per-lane vectors through a double-buffered register
-//               pipeline and reduce them against the LDS activation (int4
-//               weights: with their fp16 group scales, dequantised in the
-//               dot product).
-//   all waves   load the task's input activation into LDS after the wait (one
-//               round trip), run attention, and run inline continuations.
+//               16-byte-per-lane vectors through a ring of registers and
+//               reduce them against the LDS activation (int4 weights: with
+//               their fp16 group scales, dequantised in the dot product); they
+//               also load the task's input into LDS after the wait (one round
+//               trip), and the last one stages task records and prepares
+//               epilogues ahead.
+//   all waves   run attention and inline continuations.
 //
 // Per task the workgroup passes three barriers:
 //   B1a  the sync wave's counter wait is satisfied (or the launch aborts)
@@ -33,7 +34,7 @@
 // consumes the last granules of one task it already issues the first ones of
 // the next GEMV task of its queue (weights depend on nothing), so they travel
 // while the epilogue, the signal, the wait and the input load go on.  For that
-// the sync wave keeps the next tasks' records and layer pointers in LDS
+// the last wave keeps the next tasks' records and layer pointers in LDS
 // (struct Slot), loaded two and three tasks ahead: read when needed, each was
 // a chain of two cold scalar loads between a task's end and its successor's
 // first weight load.
@@ -47,7 +48,9 @@
 // their weight loads are in flight.
 // Lane reductions use DPP (VALU latency) rather than LDS permutes.
 //
-// No MFMA: a batch-1 GEMV is a matrix-vector product, bound by HBM bandwidth.
+// No MFMA in the GEMVs: a batch-1 GEMV is a matrix-vector product, bound by HBM
+// bandwidth.  The attention scores, of four to eight query heads against each K
+// row, are matrix products and use it.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -105,7 +108,6 @@ template <> struct Bits<2> { typedef unsigned short T; };
 template <> struct Bits<4> { typedef unsigned int T; };
 template <> struct Bits<8> { typedef unsigned int T __attribute__((ext_vector_type(2))); };
 template <> struct Bits<16> { typedef unsigned int T __attribute__((ext_vector_type(4))); };
-template <> struct Bits<64> { typedef unsigned int T __attribute__((ext_vector_type(16))); };
 
 template <typename T>
 __device__ __forceinline__ T ldg(const void* p) {
@@ -222,7 +224,7 @@ __device__ __forceinline__ float group_max(float v) {
   return v;
 }
 
-// Sum / max over the lanes l ^ k*G of a wave (G = 8, 16 or 32: the lanes that
+// Sum over the lanes l ^ k*G of a wave (G = 8, 16 or 32: the lanes that
 // share l mod G), returned to every lane.
 template <int G>
 __device__ __forceinline__ float across_sum(float v) {
@@ -232,15 +234,6 @@ __device__ __forceinline__ float across_sum(float v) {
   if constexpr (G <= 32) v = xor32_add(v);
   return v;
 }
-template <int G>
-__device__ __forceinline__ float across_max(float v) {
-  static_assert(G == 8 || G == 16 || G == 32 || G == 64, "group stride");
-  if constexpr (G == 8) v = fmaxf(v, dpp<0x128>(v));
-  if constexpr (G <= 16) v = xor16_max(v);
-  if constexpr (G <= 32) v = xor32_max(v);
-  return v;
-}
-
 // Full-wave sum / max, returned to every lane.
 __device__ __forceinline__ float wave_sum(float v) {
   v = group_sum<16>(v);
@@ -1121,8 +1114,6 @@ struct AttnGeom {
   static constexpr int MERGE = GM * 64 + 4 * NT;
   static constexpr int LDS = SCRATCH > MERGE ? SCRATCH : MERGE;
   static_assert(GM % 4 == 0 && T * 16 * GM <= GM * HD, "the weights of a pass fit a wave's part of red");
-  // floats of the queries' bf16 parts [3][group][HD] in the activation region
-  static constexpr int QPARTS = 3 * GM * HD / 2;
 };
 
 __device__ __forceinline__ float row_elem(const uint4& v, int e) {

@@ -91,3 +91,19 @@ def test_task_size_edges(fmt, rows):
     """Row caps around the 64 items an epilogue is prepared for (a row pair is
     one item): many small tasks a queue, and tasks on both sides of the line."""
     check(shape_of("g4_128", 512, 17408 if rows > 64 else 2048, 20000), fmt, 20, tuning=(0, 0, rows, 0, 0, 0, 0))
+
+
+@pytest.mark.parametrize("pos", [40, 300])
+def test_attention_scratch_in_activation_region(pos):
+    """A SwiGLU width that leaves no room for the attention scratch beside the
+    activation vector (row cap 2): it lies behind the queries inside it, for the
+    inline attention and for splits and their merge."""
+    check(shape_of("g1_64", 256, 35840, 1000, layers=1), "bf16", pos, tuning=(0, 0, 2, 0, 0, -1, 0))
+
+
+def test_activation_past_the_room_for_a_task_is_refused():
+    """Widths that were refused for lack of LDS stay refused."""
+    from paper_2606_09682_amd import amk
+    with pytest.raises(amk.AmkError) as e:
+        check(shape_of("g1_64", 256, 30720, 1000, layers=1), "bf16", 40)
+    assert e.value.status == amk.AMK_ERR_UNSUPPORTED
