@@ -1135,7 +1135,11 @@ __device__ __forceinline__ float row_elem(const uint4& v, int e) {
 // to 15 are zero).  Cut by truncation the three parts add up to the fp32 value
 // exactly, and a product of two 8-bit significands is exact in fp32, so the
 // sums differ from fp32 products only in their order.  On the vector units
-// the scores took 24 of 39 instructions per row.
+// the scores took 24 of 39 instructions per row.  The later parts are often 0
+// and the last columns always, and 0 times an infinite K element is NaN: those
+// columns count only where they are finite, and the first part's column, whose
+// parts are 0 only where the query is, then gives the +-inf or NaN of the fp32
+// product (a K row with a score of -inf has weight 0).
 // The queries are pre-multiplied by log2(e) / sqrt(d), so scores and
 // maxima are in log2 units and each softmax weight is one exp2: the same
 // weights as exp(q.k / sqrt(d) - max), up to fp32 rounding.  The weights
@@ -1183,6 +1187,9 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
   const int tid = wave * 64 + lane;
   const float* qp = m.q + (size_t)layer * m.qs + (size_t)(g * G) * HD;
   const float qscale = m.attn_scale * 1.4426950408889634f;  // log2(e) / sqrt(d)
+  // what columns past the first part's never add to a score: NaN and infinities
+  // (v_cmp_class bits 0 to 2 and 9)
+  const int not_first = col < 4 ? 0 : 0x207;
   constexpr int QN = GM * HD > NT ? 2 : 1;
   float qv[QN];
 #pragma unroll
@@ -1255,7 +1262,7 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
           // lane: column col, rows quad * 4 + i; add the parts' columns
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            float v = d[i];
+            float v = __builtin_amdgcn_classf(d[i], not_first) ? 0.f : d[i];
             v += dpp<0x128>(v);  // row_ror:8
             v += dpp<0x124>(v);  // row_ror:4
             v = tb + quad * 4 + i < n ? v : -INFINITY;

@@ -31,7 +31,7 @@ def shape_of(heads, hidden=256, inter=320, vocab=1000, layers=2, tied=False):
                                    tied_embeddings=tied)
 
 
-def check(cfg, fmt, pos, tuning=None, group=0, steps=1):
+def check(cfg, fmt, pos, tuning=None, group=0, steps=1, edit=None):
     import torch
     from paper_2606_09682_amd import amk
     w = synth.make_weights(cfg, seed=3)
@@ -42,10 +42,12 @@ def check(cfg, fmt, pos, tuning=None, group=0, steps=1):
     kv = synth.make_kv_cache(cfg, pos, seed=1, max_seq=pos + steps)
     dec = amk.Decoder(amk.make_config(**config_kwargs(cfg, fmt, pos + steps, group)), weights_to_device(w, fmt),
                       amk.amk_tuning_t(*tuning) if tuning else None)
+    model = oracle.OracleModel(w, fmt, np.float32)
+    if edit:
+        edit(model, kv)
     dkv = kv_to_device(kv)
     logits = torch.empty((cfg.vocab + 3) // 4 * 4, dtype=torch.float32, device="cuda")
     ref_kv = kv.copy()
-    model = oracle.OracleModel(w, fmt, np.float32)
     tok = 1
     for i in range(steps):
         dec.step(tok, pos + i, dkv, logits)
@@ -107,3 +109,29 @@ def test_activation_past_the_room_for_a_task_is_refused():
     with pytest.raises(amk.AmkError) as e:
         check(shape_of("g1_64", 256, 30720, 1000, layers=1), "bf16", 40)
     assert e.value.status == amk.AMK_ERR_UNSUPPORTED
+
+
+def mask_rows(model, kv, pos, rows):
+    """Makes every query head of layer 0 score the cache rows `rows` minus infinity at `pos` (token 1): one
+    element of each is an infinity, where all queries of the KV group have the same sign."""
+    cfg, p = model.cfg, "layers.0."
+    h = oracle.rmsnorm(model.embed_row(1), model.vec(p + "attn_norm"), cfg.rms_eps)
+    q = oracle.linear(model.mat(p + "wq"), h).reshape(cfg.n_kv_heads, -1, cfg.head_dim)
+    q = oracle.rope(q, pos, cfg.rope_theta)
+    for g in range(cfg.n_kv_heads):
+        least = np.where(np.abs(np.sign(q[g]).sum(0)) == len(q[g]), np.abs(q[g]).min(0), 0)
+        d = int(np.argmax(least))
+        assert least[d] > 1e-3
+        kv[0, 0, g, rows, d] = 0xff80 if q[g, 0, d] > 0 else 0x7f80
+
+
+@pytest.mark.parametrize("heads", ["g1_64", "g3_64", "g4_128", "g5_128"])
+@pytest.mark.parametrize("rows", ["one", "some", "a tile", "a wave"])
+def test_infinite_k_rows_have_no_weight(heads, rows):
+    """A K row with a score of minus infinity has weight 0 and the others keep
+    theirs, in one task of a KV group (short schedule)."""
+    pos = 450
+    which = {"one": [7], "some": list(range(0, pos, 3)), "a tile": list(range(16, 32)),
+             "a wave": [r for r in range(pos) if r // 16 % 8 == 2]}[rows]
+    check(shape_of(heads), "bf16", pos, tuning=(0, 0, 0, 0, 1 << 30, -1, 0),
+          edit=lambda model, kv: mask_rows(model, kv, pos, which))
