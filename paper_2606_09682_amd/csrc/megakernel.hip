@@ -1379,11 +1379,13 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
     float M = ml[0].x;
 #pragma unroll
     for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[w].x);
+    // rows that all score -inf leave (-inf, 0, 0), which weighs 0 in a merge
+    const float mref = M == -INFINITY ? 0.f : M;
     float l = 0.f, o = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       // a wave without rows left (-inf, 0) and no accumulators
-      const float f = __builtin_amdgcn_exp2f(ml[w].x - M);
+      const float f = __builtin_amdgcn_exp2f(ml[w].x - mref);
       l = fmaf(f, ml[w].y, l);
       o = fmaf(f, ml[w].x == -INFINITY ? 0.f : r[w], o);
     }

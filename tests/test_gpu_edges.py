@@ -135,3 +135,15 @@ def test_infinite_k_rows_have_no_weight(heads, rows):
              "a wave": [r for r in range(pos) if r // 16 % 8 == 2]}[rows]
     check(shape_of(heads), "bf16", pos, tuning=(0, 0, 0, 0, 1 << 30, -1, 0),
           edit=lambda model, kv: mask_rows(model, kv, pos, which))
+
+
+@pytest.mark.parametrize("heads", ["g1_64", "g3_64", "g4_128", "g5_128"])
+@pytest.mark.parametrize("splits,masked", [(4, "a split"), (4, "across splits"), (16, "a split"), (16, "across splits")])
+def test_infinite_k_rows_of_a_split_have_no_weight(heads, splits, masked):
+    """A split whose rows all score minus infinity adds nothing to the merge
+    (long schedule)."""
+    pos = 450
+    chunk = (pos + splits) // splits
+    which = list(range(chunk, 2 * chunk)) if masked == "a split" else list(range(0, pos, 5))
+    check(shape_of(heads), "bf16", pos, tuning=(splits, 0, 0, 0, -1, -1, 0),
+          edit=lambda model, kv: mask_rows(model, kv, pos, which))
