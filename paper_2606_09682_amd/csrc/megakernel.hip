@@ -1473,7 +1473,8 @@ __device__ __forceinline__ void attention_all(ModelRef m, int layer, int pos, co
           if constexpr (DPL == 2) d = fmaf(qv[i][1], bf_hi(kr[i][p]), d);
           d = wave_sum(d) * scale;
           const float mn = fmaxf(mrun, d);
-          const float alpha = __expf(mrun - mn), e = __expf(d - mn);
+          const float mref = mn == -INFINITY ? 0.f : mn;  // only scores of -inf so far: weight 0
+          const float alpha = __expf(mrun - mref), e = __expf(d - mref);
           l = l * alpha + e;
           acc[0] = fmaf(e, bf_lo(vr[i][p]), acc[0] * alpha);
           if constexpr (DPL == 2) acc[1] = fmaf(e, bf_hi(vr[i][p]), acc[1] * alpha);

@@ -147,3 +147,11 @@ def test_infinite_k_rows_of_a_split_have_no_weight(heads, splits, masked):
     which = list(range(chunk, 2 * chunk)) if masked == "a split" else list(range(0, pos, 5))
     check(shape_of(heads), "bf16", pos, tuning=(splits, 0, 0, 0, -1, -1, 0),
           edit=lambda model, kv: mask_rows(model, kv, pos, which))
+
+
+@pytest.mark.parametrize("heads", ["g1_64", "g3_64", "g4_128"])
+@pytest.mark.parametrize("rows", [[0], [3], [0, 1, 2], [4, 6]])
+def test_infinite_k_rows_at_the_first_positions(heads, rows):
+    """The same in the tiny schedule, also before the first row with a weight."""
+    check(shape_of(heads), "bf16", 7, tuning=(0, 0, 0, 0, 0, 8, 0),
+          edit=lambda model, kv: mask_rows(model, kv, 7, rows))
