@@ -349,13 +349,14 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
         if (t.op == AMK_OP_O || t.op == AMK_OP_DOWN) res = std::max(res, rows);
         if (rows && (items > 64 || t.op == AMK_OP_LMHEAD)) stat = std::max(stat, items * (t.op == AMK_OP_QKV ? 4 : t.op == AMK_OP_LMHEAD ? 1 : 2));
       }
-    const size_t pstride = round_up(max_rows, 4);
+    // one partial per row, one more where a streaming wave's range begins inside one
+    const size_t parts = round_up(max_rows + nsw - 1, 4);
     stat = round_up(stat, 4);
     res = round_up(res, 4);
     // the attention scratch goes behind the queries in the activation region
     // if there is no room for it beside it
     const size_t attn = (size_t)amk_internal_attn_scratch(s.group, s.hd);
-    size_t scr = std::max<size_t>((size_t)nsw * pstride, attn), scr_at = 0;
+    size_t scr = std::max(parts, attn), scr_at = 0;
     const size_t fixed = (act_lds + stat + res + xsum) * 4;
     size_t lds_bytes = fixed + scr * 4;
     int max_lds = 0;
@@ -374,7 +375,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     }
     if ((long)lds_bytes + amk_internal_static_lds() > (long)max_lds && qrows + attn <= act_lds) {
       scr_at = qrows;
-      scr = (size_t)nsw * pstride;
+      scr = parts;
       lds_bytes = fixed + scr * 4;
     }
     if ((long)lds_bytes + amk_internal_static_lds() > (long)max_lds) {
@@ -573,7 +574,6 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
       h->dsch[v].counter_bytes = r_ctr[v].bytes;
     }
     m.lds_act = (int32_t)act_lds;
-    m.part_stride = (int32_t)pstride;
     m.lds_stat = (int32_t)stat;
     m.lds_res = (int32_t)res;
     m.lds_scr = (int32_t)scr;

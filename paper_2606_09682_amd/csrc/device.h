@@ -90,7 +90,6 @@ struct DevModel {
   // part[lds_scr] xsum[lds_act / 32 under W4A16]
   int32_t lds_act;           // activation vector region in floats: a whole number of granules'
                              // elements plus one float4 of padding per 64 floats
-  int32_t part_stride;       // most rows of one GEMV task (partials per streaming wave)
   int32_t lds_stat;          // four floats per item of the largest task of more than 64 items
   int32_t lds_res;           // most rows of one O / down task
   int32_t lds_scr;           // GEMV partials of all streaming waves, or attention scratch

@@ -282,7 +282,7 @@ __device__ __forceinline__ bool is_normed(int op) {
 //   stat[...]               static epilogue data of a task of more than 64 items
 //                           (epi_stat gives the layout)
 //   res[...]                residual rows of the last O / down task
-//   part[...]               per-streaming-wave row partials / attention scratch
+//   part[...]               the streaming waves' row partials / attention scratch
 //   xsum[...]               W4A16: xsum[i] = sum of act[32 i .. 32 i + 31]
 __device__ __forceinline__ int act_at(int i) { return i + ((i >> 6) << 2); }
 // act_at(c * E + j) for a granule of E elements (a multiple of 64), j < E
@@ -825,14 +825,16 @@ __device__ __forceinline__ Ranges wave_ranges(const Gemv& g) {
   return r;
 }
 
-__device__ __forceinline__ float row_sum(const float* part, int stride, const Gemv& g, const Ranges& wr, int j) {
+// Wave sw's partial of row j lies at part[sw + j]: the waves' ranges follow each
+// other and neighbours share at most one row, so no two partials share a word.
+__device__ __forceinline__ float row_sum(const float* part, const Gemv& g, const Ranges& wr, int j) {
   const int lo = j * g.gpr, hi = lo + g.gpr;
   // every wave's slot is read (all reads in flight at once), the ones of
   // waves that wrote nothing for row j are dropped: a wave with an empty
   // range wrote nothing, even if its start lies inside the row
   float v[NSW];
 #pragma unroll
-  for (int sw = 0; sw < NSW; ++sw) v[sw] = part[sw * stride + j];
+  for (int sw = 0; sw < NSW; ++sw) v[sw] = part[sw + j];
   float s = 0.f;
 #pragma unroll
   for (int sw = 0; sw < NSW; ++sw) s += max(wr.b[sw], lo) < min(wr.b[sw + 1], hi) ? v[sw] : 0.f;
@@ -886,8 +888,8 @@ __device__ __forceinline__ void epi_qkv(ModelRef m, const Epi& e, const Lds& L, 
   const int l = e.layer;
   for (int u = e.begin + lane; u < e.end; u += 64) {
     const int j0 = 2 * (u - e.begin);
-    float y0 = row_sum(L.part, m.part_stride, e.g, e.wr, j0) * e.rs;
-    float y1 = row_sum(L.part, m.part_stride, e.g, e.wr, j0 + 1) * e.rs;
+    float y0 = row_sum(L.part, e.g, e.wr, j0) * e.rs;
+    float y1 = row_sum(L.part, e.g, e.wr, j0 + 1) * e.rs;
     const RowStat st = epi_stat<AMK_OP_QKV>(e, L, u);
     if (m.fmt == AMK_WEIGHTS_W8A16) {
       y0 *= st.a;
@@ -921,7 +923,7 @@ __device__ __forceinline__ void epi_residual(ModelRef m, const Epi& e, Res& res,
   const int xin = op == AMK_OP_O ? 2 * e.layer : 2 * e.layer + 1;
   const bool cached = res.buf == xin && res.lo == e.begin && res.hi == e.end;
   for (int r = e.begin + lane; r < e.end; r += 64) {
-    float y = row_sum(L.part, m.part_stride, e.g, e.wr, r - e.begin);
+    float y = row_sum(L.part, e.g, e.wr, r - e.begin);
     const RowStat st = epi_stat<AMK_OP_O>(e, L, r);
     if (m.fmt == AMK_WEIGHTS_W8A16) y *= st.a;
     const float x = xin == 0 ? st.c : cached ? L.res[r - e.begin] : ldg<float>(m.x + (size_t)xin * m.xs + r);
@@ -937,8 +939,8 @@ __device__ __forceinline__ void epi_residual(ModelRef m, const Epi& e, Res& res,
 __device__ __forceinline__ void epi_gateup(ModelRef m, const Epi& e, const Lds& L, int lane) {
   for (int r = e.begin + lane; r < e.end; r += 64) {
     const int j = 2 * (r - e.begin);
-    float gv = row_sum(L.part, m.part_stride, e.g, e.wr, j) * e.rs;
-    float uv = row_sum(L.part, m.part_stride, e.g, e.wr, j + 1) * e.rs;
+    float gv = row_sum(L.part, e.g, e.wr, j) * e.rs;
+    float uv = row_sum(L.part, e.g, e.wr, j + 1) * e.rs;
     if (m.fmt == AMK_WEIGHTS_W8A16) {
       const RowStat st = epi_stat<AMK_OP_GATEUP>(e, L, r);
       gv *= st.a;
@@ -958,7 +960,7 @@ __device__ __forceinline__ void epi_lmhead(ModelRef m, const Epi& e, const Lds& 
   int besti = 0x7fffffff;
   bool nan = false;
   for (int r = e.begin + lane; r < e.end; r += 64) {
-    float y = row_sum(L.part, m.part_stride, e.g, e.wr, r - e.begin) * e.rs;
+    float y = row_sum(L.part, e.g, e.wr, r - e.begin) * e.rs;
     if (m.lm_fmt == AMK_WEIGHTS_W8A16) y *= epi_stat<AMK_OP_LMHEAD>(e, L, r).a;
     stc(logits + r, y);
     nan |= y != y;
@@ -1037,22 +1039,21 @@ __device__ __forceinline__ Fast fast_prepare(ModelRef m, const Ctl& ctl, const a
   return f;
 }
 
-__device__ __forceinline__ float masked_sum(const float* part, int stride, uint32_t bits, int j) {
+__device__ __forceinline__ float masked_sum(const float* part, uint32_t bits, int j) {
   uint32_t v[NSW];
 #pragma unroll
-  for (int sw = 0; sw < NSW; ++sw) v[sw] = __float_as_uint(part[sw * stride + j]);
+  for (int sw = 0; sw < NSW; ++sw) v[sw] = __float_as_uint(part[sw + j]);
   float s = 0.f;
 #pragma unroll
   for (int sw = 0; sw < NSW; ++sw) s += __uint_as_float(v[sw] & (uint32_t)((int)(bits << (31 - sw)) >> 31));
   return s;
 }
 
-__device__ __forceinline__ void fast_finish(int op, int n, const Fast& f, float rs, const Lds& L, int pstride,
-                                            int lane) {
+__device__ __forceinline__ void fast_finish(int op, int n, const Fast& f, float rs, const Lds& L, int lane) {
   if (lane >= n) return;
   if (op == AMK_OP_QKV) {
-    const float y0 = masked_sum(L.part, pstride, f.bits, 2 * lane) * rs * f.f0;
-    const float y1 = masked_sum(L.part, pstride, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
+    const float y0 = masked_sum(L.part, f.bits, 2 * lane) * rs * f.f0;
+    const float y1 = masked_sum(L.part, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
     const bool rot = f.bits & Fast::ROT;
     const float a = rot ? y0 * f.c - y1 * f.s : y0;
     const float b = rot ? y1 * f.c + y0 * f.s : y1;
@@ -1064,12 +1065,12 @@ __device__ __forceinline__ void fast_finish(int op, int n, const Fast& f, float 
       stc((uint16_t*)(f.d0 + f.d1), f2bf(b));
     }
   } else if (op == AMK_OP_GATEUP) {
-    const float gv = masked_sum(L.part, pstride, f.bits, 2 * lane) * rs * f.f0;
-    const float uv = masked_sum(L.part, pstride, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
+    const float gv = masked_sum(L.part, f.bits, 2 * lane) * rs * f.f0;
+    const float uv = masked_sum(L.part, f.bits >> NSW, 2 * lane + 1) * rs * f.f1;
     const float silu = gv / (1.0f + __expf(-gv));
     stc((float*)f.d0, silu * uv);
   } else {
-    const float o = f.c + masked_sum(L.part, pstride, f.bits, lane) * f.f0;
+    const float o = f.c + masked_sum(L.part, f.bits, lane) * f.f0;
     stc((float*)f.d0, o);
     L.res[lane] = o;
   }
@@ -1754,7 +1755,7 @@ amk_decode_kernel(DevModel model, int32_t token, int32_t pos, uint32_t epoch, ui
         src = m.o + (size_t)layer * m.qs;
         n4 = (m.nq * HD) >> 2;
       }
-      mypart = L.part + sw * m.part_stride;
+      mypart = L.part + sw;
       next_gemv = next < qe && is_gemv(uni(ctl.slot[next & (NSLOT - 1)].t.op));
     }
     __syncthreads();
@@ -1861,13 +1862,12 @@ amk_decode_kernel(DevModel model, int32_t token, int32_t pos, uint32_t epoch, ui
           if (lane == 0) mypart[w.j] = r;
         }
       }
-      const int pstride = m.part_stride;
       __syncthreads();  // B2: partials in LDS
       traced(AMK_TRACE_COMPUTE_END);
       if (wave == 0) {
         if (!ok) return;
         if (small) {
-          fast_finish(op, end - begin, f, rs, L, pstride, lane);
+          fast_finish(op, end - begin, f, rs, L, lane);
         } else {
           switch (op) {
             case AMK_OP_QKV: epi_qkv(m, e, L, pos, kv, lane); break;

@@ -155,3 +155,11 @@ def test_infinite_k_rows_at_the_first_positions(heads, rows):
     """The same in the tiny schedule, also before the first row with a weight."""
     check(shape_of(heads), "bf16", 7, tuning=(0, 0, 0, 0, 0, 8, 0),
           edit=lambda model, kv: mask_rows(model, kv, 7, rows))
+
+
+def test_row_cap_that_fills_the_lds():
+    """544 heads of 64 under a row cap of 384: the activation vector, a task of
+    the row cap (192 q/k/v row pairs) and the staged records all fit."""
+    cfg = synth.get("tiny").with_(name="edge_544_heads", hidden=256, n_layers=1, n_heads=544, n_kv_heads=136,
+                                  head_dim=64, intermediate=320, vocab=1000)
+    check(cfg, "bf16", 20, tuning=(0, 0, 384, 0, 0, 0, 0))
