@@ -401,7 +401,6 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     size_t top = 0;
     auto take = [&](size_t bytes) { Region r{top, bytes}; top = round_up(top + bytes, 256); return r; };
     const Region r_layers = take(sizeof(DevLayer) * L);
-    const Region r_geom = take(sizeof(OpGeom) * amk::kOps);
     const Region r_rope = take(sizeof(float) * 2 * (size_t)s.max_seq * s.half);
     // vectors of the residual stream and per-layer activations on separate
     // 256-byte boundaries (64 floats)
@@ -502,22 +501,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
         rope[2 * ((size_t)p * s.half + i) + 1] = (float)std::sin(a);
       }
     }
-    // row geometry per GEMV op; a tied LM head is the bf16 embedding
-    const int lm_fmt = s.tied ? AMK_WEIGHTS_BF16 : s.fmt;
-    std::vector<OpGeom> geom(amk::kOps);
-    for (int op : {(int)AMK_OP_QKV, (int)AMK_OP_O, (int)AMK_OP_GATEUP, (int)AMK_OP_DOWN, (int)AMK_OP_LMHEAD}) {
-      const int K = op == AMK_OP_O ? s.nq * s.hd : op == AMK_OP_DOWN ? s.I : s.H;
-      const int f = op == AMK_OP_LMHEAD ? lm_fmt : s.fmt;
-      OpGeom& g = geom[op];
-      g.row_bytes = f == AMK_WEIGHTS_W4A16 ? K / 2 : f == AMK_WEIGHTS_W8A16 ? K : 2 * K;
-      g.gpr = (g.row_bytes + 1023) / 1024;
-      g.magic = g.gpr > 1 ? (uint32_t)(((1ull << 32) + g.gpr - 1) / g.gpr) : 0;
-      g.lastb = g.row_bytes - (g.gpr - 1) * 1024;
-      g.srow = f == AMK_WEIGHTS_W4A16 ? K / s.qgroup * 2 : 0;
-      g.quant = f != AMK_WEIGHTS_BF16;
-    }
-    bool ok = hipMemcpy(base + r_geom.off, geom.data(), r_geom.bytes, hipMemcpyHostToDevice) == hipSuccess &&
-              hipMemcpy(base + r_layers.off, layers.data(), r_layers.bytes, hipMemcpyHostToDevice) == hipSuccess &&
+    bool ok = hipMemcpy(base + r_layers.off, layers.data(), r_layers.bytes, hipMemcpyHostToDevice) == hipSuccess &&
               hipMemcpy(base + r_rope.off, rope.data(), r_rope.bytes, hipMemcpyHostToDevice) == hipSuccess;
     for (int v = 0; v < kVariants && ok; ++v)
       ok = hipMemcpy(base + r_tasks[v].off, h->sch[v].tasks.data(), r_tasks[v].bytes, hipMemcpyHostToDevice) ==
@@ -533,7 +517,7 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     std::memset(&m, 0, sizeof(m));
     m.H = s.H; m.L = L; m.nq = s.nq; m.nkv = s.nkv; m.hd = s.hd; m.I = s.I; m.V = s.V; m.max_seq = s.max_seq;
     m.fmt = s.fmt;
-    m.lm_fmt = lm_fmt;
+    m.lm_fmt = s.tied ? AMK_WEIGHTS_BF16 : s.fmt;  // a tied LM head is the bf16 embedding
     m.qglog2 = 0;
     while (s.qgroup && (1 << m.qglog2) < s.qgroup) ++m.qglog2;
     m.group = s.group; m.half = s.half;
@@ -552,7 +536,6 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     m.lm_w = s.tied ? w->embed : w->lm_head.w;
     m.lm_s = m.lm_fmt != AMK_WEIGHTS_BF16 ? w->lm_head.scale : nullptr;
     m.layers = (const DevLayer*)(base + r_layers.off);
-    m.geom = (const OpGeom*)(base + r_geom.off);
     m.rope = (const float2*)(base + r_rope.off);
     m.x = (float*)(base + r_x.off);
     m.q = (float*)(base + r_q.off);
@@ -579,6 +562,17 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
     m.lds_scr = (int32_t)scr;
     m.scr_at = (int32_t)scr_at;
     m.lds_bytes = (int32_t)lds_bytes;
+    for (int op : {(int)AMK_OP_QKV, (int)AMK_OP_O, (int)AMK_OP_GATEUP, (int)AMK_OP_DOWN, (int)AMK_OP_LMHEAD}) {
+      const int K = op == AMK_OP_O ? s.nq * s.hd : op == AMK_OP_DOWN ? s.I : s.H;
+      const int f = op == AMK_OP_LMHEAD ? m.lm_fmt : s.fmt;
+      OpGeom& g = m.geom[op];
+      g.row_bytes = f == AMK_WEIGHTS_W4A16 ? K / 2 : f == AMK_WEIGHTS_W8A16 ? K : 2 * K;
+      g.gpr = (g.row_bytes + 1023) / 1024;
+      g.magic = g.gpr > 1 ? (uint32_t)(((1ull << 32) + g.gpr - 1) / g.gpr) : 0;
+      g.lastb = g.row_bytes - (g.gpr - 1) * 1024;
+      g.srow = f == AMK_WEIGHTS_W4A16 ? K / s.qgroup * 2 : 0;
+      g.quant = f != AMK_WEIGHTS_BF16;
+    }
 
     const int timeout_us = tuning && tuning->timeout_us > 0 ? tuning->timeout_us : 2000000;
     h->timeout_ticks = (uint64_t)timeout_us * 100ull;  // the device wall clock runs at 100 MHz

@@ -63,7 +63,6 @@ struct DevModel {
   const void* lm_w;
   const void* lm_s;
   const DevLayer* layers;    // device array [L]
-  const OpGeom* geom;        // device array [kOps]
   // handle-owned tables and scratch
   const float2* rope;        // [max_seq][half] (cos, sin), computed in fp64 on the host
   // Every vector below is written at most once per launch and read only after
@@ -95,6 +94,7 @@ struct DevModel {
   int32_t lds_scr;           // GEMV partials of all streaming waves, or attention scratch
   int32_t scr_at;            // offset of the attention scratch inside act, 0: it lies in part
   int32_t lds_bytes;         // dynamic LDS bytes of one workgroup
+  OpGeom geom[kOps];         // weight-row geometry per op
 };
 
 // Launch the decode-step megakernel (defined in megakernel.hip): `tiny` selects

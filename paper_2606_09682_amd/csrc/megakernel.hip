@@ -87,7 +87,7 @@ static_assert(sizeof(amk_task_t) == 64 && sizeof(DevLayer) == 128, "one dword pe
 
 struct Ctl {
   Slot slot[NSLOT];
-  OpGeom geom[kOps];            // per op, from the handle's table
+  OpGeom geom[kOps];            // per op, from the model record
   float4 prep[2][64];           // the prepared epilogue of the task to come (struct Fast), a lane per item
   float ssq[NSW];               // per-wave sum of squares of the task input
   int abort;
@@ -1653,7 +1653,8 @@ amk_decode_kernel(DevModel model, int32_t token, int32_t pos, uint32_t epoch, ui
   if (wave == 1) {
     constexpr int N = sizeof(ctl.geom) / 4;
     static_assert(N <= 64, "one dword per lane");
-    if (lane < N) reinterpret_cast<dword*>(ctl.geom)[lane] = ldg<uint32_t>((const uint32_t*)mp->geom + lane);
+    const AMK_CONST uint32_t* geom = (const AMK_CONST uint32_t*)mp->geom;
+    if (lane < N) reinterpret_cast<dword*>(ctl.geom)[lane] = geom[lane];
   } else if (wave == NW - 1) {
     // the first three records (48 lanes), then the layers of the first two
     if (lane < 48) slot_dw(qb + (lane >> 4))[lane & 15] = ldg<uint32_t>(rec_dw(qb + (lane >> 4)) + (lane & 15));

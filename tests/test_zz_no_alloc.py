@@ -91,3 +91,16 @@ def test_static_handle_limits(env):
     dec.reset()
     assert dec.status() == amk.AMK_OK
     dec.close()
+
+
+def test_static_handle_fills_the_array(env):
+    """The longest context of a static tiny decoder: its RoPE table takes 256
+    bytes a position, and 255885 positions beside the other regions are the 64
+    MiB exactly on 256 CUs."""
+    amk, torch = env
+    cfg = synth.get("tiny")
+    tensors = weights_to_device(synth.make_weights(cfg, seed=0), "bf16")
+    amk.Decoder(amk.make_config(**config_kwargs(cfg, "bf16", 255885)), tensors, static=True).close()
+    with pytest.raises(amk.AmkError) as e:
+        amk.Decoder(amk.make_config(**config_kwargs(cfg, "bf16", 255886)), tensors, static=True)
+    assert e.value.status == amk.AMK_ERR_OUT_OF_MEMORY
