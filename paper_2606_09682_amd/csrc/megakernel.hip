@@ -1159,7 +1159,10 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
   const int col = lane & 15, quad = lane >> 4;
   const int sub = lane / LPR, c = lane % LPR;  // V: row within a load, 8-dim block
   const size_t hs = (size_t)m.max_seq * HD;
-  // uniform bases and 32-bit byte offsets per lane
+  // uniform bases, of row w0, and 32-bit byte offsets per lane from them; the
+  // bases move on every WINDOW rows (a head's rows may take more than 2^32 bytes)
+  constexpr int WINDOW = 1 << 16;
+  static_assert((WINDOW + RP) * (2 * HD) < 1 << 30, "byte offsets from the bases");
   const uint8_t* Kp = (const uint8_t*)(kv + ((size_t)(layer * 2 + 0) * m.nkv + g) * hs + (size_t)j0 * HD);
   const uint8_t* Vp = (const uint8_t*)(kv + ((size_t)(layer * 2 + 1) * m.nkv + g) * hs + (size_t)j0 * HD);
   float* red = scr;                   // [NW][GM][HD]
@@ -1197,14 +1200,20 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
   for (int i = 0; i < QN; ++i) qv[i] = ldg<float>(qp + min(tid + i * NT, G * HD - 1));
   bf16x8 qf[HS][KL];
 
+  int w0 = 0;
   for (int p0 = 0; p0 < n; p0 += RP) {
+    if (p0 - w0 >= WINDOW) {
+      Kp += (size_t)(p0 - w0) * (2 * HD);
+      Vp += (size_t)(p0 - w0) * (2 * HD);
+      w0 = p0;
+    }
     // tile t of this wave: rows p0 + (t * NW + wave) * 16 ..; rows past the
     // range re-read its last row, whose weight is set to 0
     uint4 kr[T][KL], vr[T][KL];
     auto load_v = [&](int t, int tb) {
 #pragma unroll
       for (int j = 0; j < KL; ++j) {
-        const uint32_t vo = (uint32_t)(min(tb + j * VR + sub, n - 1) * (2 * HD) + c * 16);
+        const uint32_t vo = (uint32_t)((min(tb + j * VR + sub, n - 1) - w0) * (2 * HD) + c * 16);
         vr[t][j] = nt ? ldnt<uint4>(Vp + vo) : ldg<uint4>(Vp + vo);
       }
     };
@@ -1212,7 +1221,7 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
     for (int t = 0; t < T; ++t) {
       const int tb = p0 + (t * NW + wave) * 16;
       if (tb < n) {
-        const uint32_t ko = (uint32_t)(min(tb + col, n - 1) * (2 * HD) + quad * 16);
+        const uint32_t ko = (uint32_t)((min(tb + col, n - 1) - w0) * (2 * HD) + quad * 16);
 #pragma unroll
         for (int kb = 0; kb < KL; ++kb) kr[t][kb] = nt ? ldnt<uint4>(Kp + ko + kb * 64) : ldg<uint4>(Kp + ko + kb * 64);
         if (t == 0) load_v(t, tb);

@@ -163,3 +163,11 @@ def test_row_cap_that_fills_the_lds():
     cfg = synth.get("tiny").with_(name="edge_544_heads", hidden=256, n_layers=1, n_heads=544, n_kv_heads=136,
                                   head_dim=64, intermediate=320, vocab=1000)
     check(cfg, "bf16", 20, tuning=(0, 0, 384, 0, 0, 0, 0))
+
+
+@pytest.mark.parametrize("heads", ["g1_64", "g4_128", "g8_128"])
+@pytest.mark.parametrize("splits,pos", [(0, 65536), (0, 140001), (2, 140001)])
+def test_contexts_past_an_offset_window(heads, splits, pos):
+    """Rows are addressed by 32-bit offsets from bases that move on every 65536
+    rows of a task: one task of a group (short schedule) and splits."""
+    check(shape_of(heads, layers=1), "bf16", pos, tuning=(splits, 0, 0, 0, -1 if splits else 1 << 30, -1, 0))
