@@ -5,11 +5,14 @@ three tiles per wave and pass (by head size and query group), and cuts every
 fp32 query into three bf16 parts; a wave's weight stream runs on from one task
 into the next, with rings shorter and longer than a task; a task's epilogue is
 prepared ahead for up to 64 items.  Bar: the greedy token, and logits within
-2e-4 of the largest logit.  All sums are fp32 (about 1e-6 of it each through
-two layers); what is left is an appended K / V element whose bf16 rounding the
-other order of summation flips (2^-8 of one element of one averaged row, so at
-most about 2^-8 / sqrt(64) of an attention output at position 0, less behind
-the residual stream and at later positions)."""
+2e-4 of the largest logit, 5e-3 where decoding starts below position 8.  All
+sums are fp32 (1e-7 to 4e-6 of the largest logit where nothing else differs);
+what is left are appended K / V elements whose bf16 rounding the other order of
+summation flips.  A flip is 2^-8 of one of the d elements of a row that weighs
+about 1 / (pos + 1): some 2^-8 / sqrt(64) = 4.9e-4 of an attention output at
+position 0, a few of them at once where wide inputs make flips more likely, and
+2^-8 / sqrt(64) / 9 = 5e-5 from position 8 on.  The largest seen are 1.05e-3
+(hidden 7232, position 3) and 1.05e-4 (hidden 7232, position 101)."""
 import numpy as np
 import pytest
 
@@ -83,16 +86,33 @@ def test_split_and_merge_edges(heads, splits, pos):
 def test_stream_and_epilogue_edges(fmt, group, hidden, inter, vocab):
     """Ranges shorter and longer than the ring, short last granules, LM-head
     tasks of one row and of several, and a hidden size whose RMSNorm gains do not
-    all fit a wave's preload; steps from position 0 (tiny, then short schedule)."""
+    all fit a wave's preload; steps from position 0 (tiny, then short schedule),
+    and over a filled cache, under the bar of later positions."""
     check(shape_of("g3_64", hidden, inter, vocab), fmt, 0, group=group, steps=8)
+    check(shape_of("g3_64", hidden, inter, vocab), fmt, 100, group=group, steps=2)
 
 
-@pytest.mark.parametrize("rows", [2, 24, 64, 66, 130])
+@pytest.mark.parametrize("rows", [2, 24, 64, 66, 128, 130])
 @pytest.mark.parametrize("fmt", ["bf16", "w8a16"])
 def test_task_size_edges(fmt, rows):
-    """Row caps around the 64 items an epilogue is prepared for (a row pair is
-    one item): many small tasks a queue, and tasks on both sides of the line."""
+    """Many small tasks a queue, and gate/up tasks on both sides of the 64 items
+    an epilogue is prepared for (a row pair is one item): 1, 8, 8, 33, 64 and 64
+    or 65 of them under these row caps."""
     check(shape_of("g4_128", 512, 17408 if rows > 64 else 2048, 20000), fmt, 20, tuning=(0, 0, rows, 0, 0, 0, 0))
+
+
+@pytest.mark.parametrize("fmt,group", [("bf16", 0), ("w8a16", 0), ("w4a16", 32)])
+@pytest.mark.parametrize("pos", [3, 40])
+@pytest.mark.parametrize("op,assign", [("qkv", 0), ("residual", 0), ("residual", 1)])
+def test_large_task_epilogues(op, assign, pos, fmt, group):
+    """q/k/v tasks of 96 row pairs (136 KV heads) and O / down tasks of 64 and 65
+    rows (hidden 16416), in the tiny and the short schedule; with the queues
+    assigned by cost, O and down tasks of one queue own different rows, so the
+    residual is not the queue's own."""
+    cfg = shape_of("g1_64", 16416 if op == "residual" else 256)
+    if op == "qkv":
+        cfg = cfg.with_(name="edge_136_heads", n_heads=136, n_kv_heads=136)
+    check(cfg, fmt, pos, tuning=(0, 0, 0, 0, 0, 0, assign), group=group)
 
 
 @pytest.mark.parametrize("pos", [40, 300])
