@@ -89,7 +89,8 @@ struct DevModel {
   // part[lds_scr] xsum[lds_act / 32 under W4A16]
   int32_t lds_act;           // activation vector region in floats: a whole number of granules'
                              // elements plus one float4 of padding per 64 floats
-  int32_t lds_stat;          // four floats per item of the largest task of more than 64 items
+  int32_t lds_stat;          // static data of the largest LM-head task, and of tasks of more than 64
+                             // items: per item 4 floats (QKV), 2 (gate/up, O, down) or 1 (LM head)
   int32_t lds_res;           // most rows of one O / down task
   int32_t lds_scr;           // GEMV partials of all streaming waves, or attention scratch
   int32_t scr_at;            // offset of the attention scratch inside act, 0: it lies in part

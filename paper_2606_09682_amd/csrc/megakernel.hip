@@ -65,14 +65,12 @@ constexpr int NT = 512;       // threads per workgroup
 constexpr int NW = NT / 64;   // waves
 constexpr int NSW = NW - 1;   // streaming waves
 constexpr int GRAN = 1024;    // bytes per wave-wide 16-B-per-lane load
-// Granules each streaming wave keeps in flight (registers): R slots, each
+// Granules each streaming wave keeps in flight (registers): slots, each
 // refilled as soon as it is consumed.  28 KiB a CU; more only lengthens every
 // queue that polls, inputs and result stores pass through.  Llama-3-8B shape,
-// us a step with R = 4 / 5 / 6 / 8: bf16 pos 0 2808 / 2834 / 2836 / 2856, W8A16
+// us a step with 4 / 5 / 6 / 8: bf16 pos 0 2808 / 2834 / 2836 / 2856, W8A16
 // pos 100 1826 / 1818 / 1823 / 1841, W4A16 pos 2000 1755 / 1785 / 1827 / 1792.
-template <int FMT> struct Ring {
-  static constexpr int R = 4;
-};
+constexpr int RING = 4;
 // int4 columns per granule, and per lane (one 16-byte load of 32 nibbles)
 constexpr int GRAN4 = 2 * GRAN;
 constexpr int LANE4 = 32;
@@ -685,7 +683,7 @@ struct RowStat {
   float c = 0.f, s = 0.f;  // QKV: RoPE factors;  layer-0 O: c = the embedding value
 };
 
-// Item i of a task: its (first) row's matrix and row, and the second row's.
+// Static data of item i of the task at slot sl.
 __device__ __forceinline__ RowStat row_stat(ModelRef m, const Slot& sl, int op, int quant, int i, int token,
                                             int pos) {
   RowStat r;
@@ -1181,10 +1179,18 @@ __device__ __forceinline__ void attention(ModelRef m, int layer, int g, int j0, 
     for (int e = 0; e < 8; ++e) acc[h][e] = 0.f;
 
   const bool active = wave * 16 < n;  // this wave has rows
-  // long splits stream their rows past the caches like the weights (Llama-3.2-1B
-  // W8A16 at position 4096, 129 rows a split: 689 us a step, 679 so); a short
-  // context is found in them again at the next step (SmolLM2 at position 200,
-  // one task of 201 rows a group: 677, and 692 with non-temporal loads)
+  // Long splits load their rows past the caches like the weights.  us a step,
+  // plain / non-temporal, with the rows cold (three models decoded in turn):
+  // Llama-3.2-1B W8A16, 64 / 96 / 129 rows a split: 637 / 640, 656 / 649, 667 /
+  // 656; TinyLlama bf16, 48 / 64 / 96: 871 / 874, 880 / 875, 909 / 898; SmolLM2
+  // bf16, 32 / 64 / 96: 743 / 748, 760 / 749, 785 / 766.  Where one context is
+  // decoded on, the memory-side cache holds its rows until they outgrow its 256
+  // MB, and plain loads win: the same at 96 rows 644 / 651, 888 / 899 and 756 /
+  // 768, at 128 rows 648 / 654, 893 / 904 and 763 / 773; 8B bf16 at 96 and 256
+  // rows (403 and 1074 MB) 2983 / 2957 and 3072 / 3053.  At 96 rows what the
+  // cold rows gain outweighs or equals what the cached ones lose.  A group's rows
+  // in one task (no record) are slower non-temporally at any length (SmolLM2,
+  // 201 rows: 656 / 672; 8B, 8192: 6246 / 6725).
   const bool nt = record && n >= 96;
   // a thread's queries (one or two of the group's G * HD), loaded ahead of the
   // rows; each is cut once and its parts go to qs[part][G * HD] as bf16
@@ -1610,7 +1616,7 @@ template <int HD, int GM, int FMT, bool TINY>
 __global__ void __launch_bounds__(NT, 1) __attribute__((aligned(65536)))
 amk_decode_kernel(DevModel model, int32_t token, int32_t pos, uint32_t epoch, uint16_t* __restrict__ kv,
                   float* __restrict__ logits, uint64_t timeout_ticks) {
-  constexpr int R = Ring<FMT>::R;
+  constexpr int R = RING;
   extern __shared__ float4 lds4[];
   __shared__ Ctl ctl;
   const AMK_CONST DevModel* mp = (const AMK_CONST DevModel*)__builtin_amdgcn_kernarg_segment_ptr();  // `model`

@@ -55,10 +55,21 @@ struct Schedule {
   int n_lm_slots = 0;              // argmax partial slots (one per LM-head task)
 };
 
-// Defaults of amk_tuning_t.short_context and .tiny_context (measured crossovers
-// on the 8B shape: the tiny schedule gains about 140 us at pos 0 and breaks
-// even near pos 6, where its per-task attention catches up with the saved
-// stage).
+// Defaults of amk_tuning_t.short_context and .tiny_context.  us a step by the
+// position, with either schedule:
+//  tiny / short   Llama-3-8B bf16: 0 2732 / 2780, 3 2777 / 2782, 5 2808 / 2780;
+//                 8B W8A16: 0 1681 / 1745, 4 1741 / 1746, 5 1757 / 1746;
+//                 Llama-3.2-1B W8A16: 0 557 / 583, 4 584 / 583, 5 591 / 583;
+//                 TinyLlama bf16: 0 690 / 746, 5 737 / 747, 6 748 / 747;
+//                 SmolLM2 bf16: 0 542 / 619, 5 590 / 618, 7 613 / 619.
+//                 Even near 3, 4, 4, 6 and past 7: 6 loses up to 1.4% at positions
+//                 4 and 5 of the larger shapes and gains up to 12% before.
+//  short / long   8B bf16: 255 2877 / 2914, 300 2885 / 2914, 400 2939 / 2915;
+//                 8B W8A16: 255 1845 / 1866, 300 1858 / 1866, 400 1910 / 1865;
+//                 Llama-3.2-1B W8A16: 300 612 / 633, 400 632 / 634, 600 653 / 634;
+//                 TinyLlama bf16: 400 840 / 861, 600 880 / 864;
+//                 SmolLM2 bf16: 400 710 / 739, 600 751 / 741.
+//                 Even between 310 and 560: 256 lies below all of them.
 constexpr int kDefaultShortContext = 256;
 constexpr int kDefaultTinyContext = 6;
 
