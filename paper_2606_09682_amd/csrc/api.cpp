@@ -365,7 +365,8 @@ static int create_impl(const amk_config_t* cfg, const amk_weights_t* w, const am
       return AMK_ERR_DEVICE;
     }
     // the shapes taken are those whose activation leaves room for a task of the
-    // row cap: partials, two static values and a residual per row
+    // row cap: two static values, a residual and a partial per row and wave (the
+    // partials lie compactly, which saves more than the kernel's own LDS takes)
     const size_t cap = round_up((size_t)s.max_jobs, 4);
     const size_t room = (act + act / 16 + 3 * cap + std::max((size_t)nsw * cap, attn) + xsum) * 4;
     if ((long)room + 256 > (long)max_lds) {
